@@ -93,8 +93,6 @@ struct Carve {
   }
 };
 
-constexpr int DECODE_MAX_SPLITS = 16;
-
 struct LayerBufs {
   void *n1, *q, *k, *v, *o, *xt;
   uint8_t *mode, *bit;
@@ -138,7 +136,7 @@ tr::KvWs carve_kv(Carve &cv, const triroute_cfg &c, int B, int T) {
   return w;
 }
 float *carve_attn_decode(Carve &cv, const triroute_cfg &c, int B) {
-  return cv.take<float>(size_t(B) * c.n_heads * DECODE_MAX_SPLITS * (c.head_dim + 2));
+  return cv.take<float>(tr::decode_part_floats(c, B));
 }
 
 LayerBufs carve_layer(Carve &cv, const triroute_cfg &c, int B, int T) {

@@ -547,6 +547,7 @@ struct DecodeArgs {
 // issuing tiles, across pool boundaries, for as long as free ring space
 // allows.  The block's 8 rings plus a few words fill the 160 KB of LDS.
 constexpr int DEC_WAVES = 8;
+constexpr int DEC_MAX_SPLITS = 32;
 // Relative cost of a tile of width index bi in the wave split (bytes moved
 // plus dequantisation work, 2 / 4 / 8 / 16 bits).
 __device__ constexpr int DEC_COST[4] = {4, 6, 9, 13};
@@ -1121,6 +1122,12 @@ __global__ __launch_bounds__(512, 1) void attn_decode_kernel(DecodeArgs a) {
   }
 }
 
+// Merge of a row's NS chunk partials: one wave per (sequence, head).  The
+// launch is a latency chain, so every load is issued before the first is
+// used: lane j < NS takes (m, l) of chunk j, and each lane its channels of
+// the chunks, CMB_U of them in flight.  (Walking the chunks one by one cost
+// 14.4 us for 16 chunks of 48 rows, against 4 us here.)
+constexpr int CMB_U = 8;
 template <int DH>
 __global__ __launch_bounds__(256) void attn_decode_combine_kernel(const float *__restrict__ part,
                                                                   int BH, int NS,
@@ -1129,19 +1136,28 @@ __global__ __launch_bounds__(256) void attn_decode_combine_kernel(const float *_
   const int lane = threadIdx.x & 63;
   if (item >= BH) return;
   const float *pp = part + int64_t(item) * NS * (DH + 2);
-  float M = -INFINITY;
-  for (int j = 0; j < NS; ++j) M = fmaxf(M, pp[j * (DH + 2)]);
-  float L = 0.f, acc[DH / 64];
+  const bool in = lane < NS;  // NS <= DEC_MAX_SPLITS < 64
+  const float mj = in ? pp[lane * (DH + 2)] : -INFINITY;
+  const float lj = in ? pp[lane * (DH + 2) + 1] : 0.f;
+  const float M = wave_max(mj);
+  // a chunk without keys has m = -inf: weight 0
+  const float wj = mj == -INFINITY ? 0.f : exp2f(mj - M);
+  const float L = wave_sum(lj * wj);
+  float acc[DH / 64];
 #pragma unroll
   for (int r = 0; r < DH / 64; ++r) acc[r] = 0.f;
-  if (M != -INFINITY) {
-    for (int j = 0; j < NS; ++j) {
-      const float mj = pp[j * (DH + 2)];
-      if (mj == -INFINITY) continue;
-      const float wgt = exp2f(mj - M);
-      L += pp[j * (DH + 2) + 1] * wgt;
+  for (int j0 = 0; j0 < NS; j0 += CMB_U) {
+    float v[CMB_U][DH / 64];
 #pragma unroll
-      for (int r = 0; r < DH / 64; ++r) acc[r] += pp[j * (DH + 2) + 2 + lane + 64 * r] * wgt;
+    for (int u = 0; u < CMB_U; ++u)
+#pragma unroll
+      for (int r = 0; r < DH / 64; ++r)
+        v[u][r] = j0 + u < NS ? pp[(j0 + u) * (DH + 2) + 2 + lane + 64 * r] : 0.f;
+#pragma unroll
+    for (int u = 0; u < CMB_U; ++u) {
+      const float wgt = __shfl(wj, j0 + u, 64);
+#pragma unroll
+      for (int r = 0; r < DH / 64; ++r) acc[r] += v[u][r] * wgt;
     }
   }
   const float inv = L > 0.f ? 1.f / L : 0.f;
@@ -1765,12 +1781,26 @@ __global__ __launch_bounds__(64 * PF_WAVES) __attribute__((amdgpu_waves_per_eu(2
 }
 
 // ------------------------------------------------------------------ launchers
+// Chunks per sequence.  A block takes a whole CU, so BH = B Hkv pairs get
+// 256 / BH chunks, rounded down: a block more than the CUs starts a second
+// round (12 pairs of 50001 tokens, with the combine: 16 chunks 31.8 us, 20
+// 29.4 us, 24 38.4 us; 88 pairs of 16000: 2 chunks 60.0 us, 3 68.4 us; 200
+// pairs of 8000: one 35.6 us, 2 45.2 us).  A chunk keeps at least 6 tiles
+// (the cache's capacity bounds them): below that its start-up costs more
+// than the split saves (3 pairs of 3000 tokens, 47 tiles: 2 chunks 15.4 us,
+// 4 12.4 us, 8 11.5 us, 16 11.6 us), and two chunks do not pay for the
+// combine's launch (3 pairs of 501 tokens: 16 chunks 24 us, one 11 us).
 int decode_splits(int B, int Hkv, int capacity, int TS) {
-  (void)capacity;
-  (void)TS;
-  // one 8-wave block per CU: chunks so that the grid covers the 256 CUs
-  const int ns = (256 + B * Hkv - 1) / (B * Hkv);
-  return max(1, min(ns, 16));
+  const int tiles = (capacity + TS - 1) / TS;
+  const int ns = max(1, min(256 / (B * Hkv), DEC_MAX_SPLITS));
+  return ns <= tiles / 6 ? ns : tiles / 6 < 3 ? 1 : tiles / 6;
+}
+
+// (16 chunks a pair from 16 pairs on: what the composite's workspace was
+// sized for; 256 / 16 is the most that rule gives there)
+size_t decode_part_floats(const triroute_cfg &cfg, int B) {
+  const int ns = B * cfg.n_kv_heads < 16 ? DEC_MAX_SPLITS : 16;
+  return size_t(B) * cfg.n_heads * ns * (cfg.head_dim + 2);
 }
 
 hipError_t launch_attn_mfma_decode(const triroute_cfg &cfg, const CacheView &cv, int B,

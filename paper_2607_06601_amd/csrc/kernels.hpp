@@ -105,6 +105,8 @@ hipError_t launch_attn_valu_decode(const triroute_cfg &cfg, const CacheView &cv,
                                    void *o, hipStream_t st);
 // attn_mfma.hip (bf16)
 int decode_splits(int B, int Hkv, int capacity, int TS);
+// floats of the decode attention's chunk partials
+size_t decode_part_floats(const triroute_cfg &cfg, int B);
 hipError_t launch_attn_mfma_decode(const triroute_cfg &cfg, const CacheView &cv, int B,
                                    const int32_t *seq_ids, const void *q, const uint8_t *mode,
                                    void *o, float *part, hipStream_t st);
