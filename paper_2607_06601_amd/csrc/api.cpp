@@ -441,12 +441,14 @@ int check_paged_args(int n_seq, int capacity, int PT, const int32_t *np) {
 
 hipError_t run_attn_prefill(const triroute_cfg &c, const triroute_kv_cache &kc, int B, int T,
                             const int32_t *seq_ids, const void *q, const uint8_t *mode,
-                            const triroute_compaction &cmp, void *o, hipStream_t st) {
+                            const triroute_compaction &cmp, void *o, float *part,
+                            size_t part_bytes, hipStream_t st) {
   // the rows no attention block writes: skipped heads, dropped rows
   hipError_t e = tr::launch_attn_zero_rows(c, B, T, mode, seq_ids, kc.n_seq, o, st);
   if (e != hipSuccess) return e;
   const tr::CacheView v = tr::make_view(c, kc);
-  return c.act == TRIROUTE_BF16 ? tr::launch_attn_mfma_prefill(c, v, B, T, seq_ids, q, cmp, o, st)
+  return c.act == TRIROUTE_BF16 ? tr::launch_attn_mfma_prefill(c, v, B, T, seq_ids, q, mode, cmp, o, part,
+                                                                 part_bytes, st)
                                 : tr::launch_attn_valu_prefill(c, v, B, T, seq_ids, q, cmp, o, st);
 }
 
@@ -877,7 +879,9 @@ int triroute_attn_prefill(const triroute_cfg *cfg, int B, int T, const int32_t *
           "NULL argument");
   TRY(check_aligned({q, o}));
   TRY(check_ws(*cfg, TRIROUTE_OP_ATTN_PREFILL, B, T, ws, ws_bytes));
-  CHECK_HIP(run_attn_prefill(*cfg, *cache, B, T, seq_ids, q, mode, *cmp, o, (hipStream_t)stream),
+  // (the call takes no workspace, so its key ranges are never split)
+  CHECK_HIP(run_attn_prefill(*cfg, *cache, B, T, seq_ids, q, mode, *cmp, o, nullptr, 0,
+                             (hipStream_t)stream),
             "attn_prefill launch");
   return TRIROUTE_OK;
 }
@@ -1003,7 +1007,10 @@ static int layer_impl(const triroute_cfg *cfg, int B, int T, bool decode, const 
     CHECK_HIP(run_attn_decode(*cfg, *cache, B, seq_ids, L.q, L.mode, L.o, part, st),
               "attn_decode launch");
   } else {
-    CHECK_HIP(run_attn_prefill(*cfg, *cache, B, T, seq_ids, L.q, L.mode, L.cmp, L.o, st),
+    // the scratch the expert block uses later holds the attention's partials
+    CHECK_HIP(run_attn_prefill(*cfg, *cache, B, T, seq_ids, L.q, L.mode, L.cmp, L.o,
+                               (float *)((uint8_t *)ws + scratch_at),
+                               op_bytes(*cfg, TRIROUTE_OP_MOE, B, T), st),
               "attn_prefill launch");
   }
   CHECK_HIP(tr::launch_oproj(*cfg, N, x, L.o, *dw, L.xt, st), "oproj launch");

@@ -1171,7 +1171,9 @@ struct PrefillArgs {
   const bf16 *q;
   const int32_t *seq_ids, *cnt, *idx;
   bf16 *o;
+  float *part;  // [B*T*H][NS]: rows of a split mode, m, l (stride 2), then O (stride DH)
   int B, T, H, Hkv, R, NQ, w, QT;  // NQ = head quartets per kv head, QT = ceil(T / 16)
+  int NS, nsf, nsl;  // partials per row; chunks of a full-mode and of a local-mode block
   float scale2;
 };
 
@@ -1184,7 +1186,12 @@ struct PrefillArgs {
 // shared by the two waves (each tile followed by its slots' key positions;
 // the transfers split over the waves), and every wave masks per head and key
 // by position.  A head whose columns all miss a tile skips it.
+// Few query tiles behind a long context leave most of the chip idle while
+// each block walks its keys; the key range of a block is then cut into chunks
+// that leave (m, l, O) partials in a.part, merged by
+// attn_prefill_combine_kernel (pf_chunks decides).
 constexpr int PF_WAVES = 2;
+constexpr int PF_MAX_CHUNKS = 8;
 constexpr int PF_HEADS = 2;                    // heads per wave
 constexpr int PF_RING = 40 * 1024 - 512;       // four blocks (eight waves) per CU
 // Lazy rescale threshold (log2 units): P' = fp16(p * s_v) with p <= 2^PF_TAU
@@ -1681,11 +1688,14 @@ __global__ __launch_bounds__(64 * PF_WAVES) __attribute__((amdgpu_waves_per_eu(2
   // heavy blocks first: full mode, and within a mode the query tiles from
   // the latest down, each across all (sequence, kv head, quartet), so that
   // blocks start in decreasing order of their key range
-  const int per_qt = a.B * a.Hkv * a.NQ, per_mode = per_qt * a.QT;
-  const int m = int(blockIdx.x) < per_mode ? TRIROUTE_FULL : TRIROUTE_LOCAL;
-  int r = int(blockIdx.x) % per_mode;
+  const int pairs = a.B * a.Hkv * a.NQ, fulls = pairs * a.nsf * a.QT;
+  const int m = int(blockIdx.x) < fulls ? TRIROUTE_FULL : TRIROUTE_LOCAL;
+  const int ns = m == TRIROUTE_FULL ? a.nsf : a.nsl, per_qt = pairs * ns;
+  int r = m == TRIROUTE_FULL ? int(blockIdx.x) : int(blockIdx.x) - fulls;
   const int qt = a.QT - 1 - r / per_qt;
   r %= per_qt;
+  const int chunk = r / pairs;
+  r %= pairs;
   const int quart = r % a.NQ;
   r /= a.NQ;
   const int g = r % a.Hkv, b = r / a.Hkv;
@@ -1747,6 +1757,21 @@ __global__ __launch_bounds__(64 * PF_WAVES) __attribute__((amdgpu_waves_per_eu(2
     w0.set(bi, sa < sb ? sa / TS : 0);
     w1.set(bi, sa < sb ? (sb + TS - 1) / TS : 0);
   }
+  if (ns > 1) {
+    // this chunk's even share of the tiles, the pools taken as one list
+    int tot = 0;
+#pragma unroll
+    for (int bi = 0; bi < 4; ++bi) tot += w1[bi] - w0[bi];
+    const int ca = tot * chunk / ns, cb = tot * (chunk + 1) / ns;
+    int at = 0;
+#pragma unroll
+    for (int bi = 0; bi < 4; ++bi) {
+      const int t0 = w0[bi], n = w1[bi] - t0;
+      w0.set(bi, t0 + min(max(ca - at, 0), n));
+      w1.set(bi, t0 + min(max(cb - at, 0), n));
+      at += n;
+    }
+  }
   SoftState<DH> st[PF_HEADS];
 #pragma unroll
   for (int hq = 0; hq < PF_HEADS; ++hq) state_init(st[hq]);
@@ -1771,13 +1796,67 @@ __global__ __launch_bounds__(64 * PF_WAVES) __attribute__((amdgpu_waves_per_eu(2
       const float lc = __shfl(st[hq].l, col, 64);
       const int jj = qt * 16 + col;
       if (jj >= count[hq]) continue;
-      const int tt = lst[jj];
+      const int64_t row = int64_t(b * a.T + lst[jj]) * a.H + h;
+      if (ns > 1) {
+        const float mc = __shfl(st[hq].m, col, 64);
+        float *ml = a.part + (row * a.NS + chunk) * 2;
+        float *po = a.part + int64_t(a.B) * a.T * a.H * a.NS * 2 + (row * a.NS + chunk) * DH;
+        if (n16 == 0) *(float2 *)ml = make_float2(mc, lc);
+#pragma unroll
+        for (int cbk = 0; cbk < DH / 16; ++cbk) po[n16 + 16 * cbk] = st[hq].O[cbk][i];
+        continue;
+      }
       const float inv = lc > 0.f ? 1.f / lc : 0.f;
-      bf16 *orow = a.o + (int64_t(b * a.T + tt) * a.H + h) * DH;
+      bf16 *orow = a.o + row * DH;
 #pragma unroll
       for (int cbk = 0; cbk < DH / 16; ++cbk) orow[n16 + 16 * cbk] = f2bf(st[hq].O[cbk][i] * inv);
     }
   }
+}
+
+// Merge of the prefill chunks of the rows whose mode was split: one wave per
+// (token, head) row of a.part, every chunk's loads in flight together.  A
+// chunk in which a column met no key has l = 0 and a state that weighs
+// nothing against the running max of one that did.
+template <int DH>
+__global__ __launch_bounds__(256) void attn_prefill_combine_kernel(PrefillArgs a,
+                                                                   const uint8_t *__restrict__ mode) {
+  const int64_t rows = int64_t(a.B) * a.T * a.H, row = int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  if (row >= rows) return;
+  const int md = mode[row];
+  const int ns = md == TRIROUTE_FULL ? a.nsf : md == TRIROUTE_LOCAL ? a.nsl : 1;
+  if (ns <= 1) return;  // the attention block wrote the row itself (or it is zero)
+  const int b = int(row / (int64_t(a.T) * a.H));
+  const int s = a.seq_ids ? a.seq_ids[b] : b;
+  if (s < 0 || s >= a.cv.n_seq) return;
+  const float2 *ml = (const float2 *)a.part + row * a.NS;
+  const float *po = a.part + rows * a.NS * 2 + row * a.NS * DH;
+  float v[PF_MAX_CHUNKS][DH / 64], m[PF_MAX_CHUNKS], l[PF_MAX_CHUNKS];
+#pragma unroll
+  for (int j = 0; j < PF_MAX_CHUNKS; ++j) {
+    const float2 t = j < ns ? ml[j] : make_float2(M0, 0.f);
+    m[j] = t.x;
+    l[j] = t.y;
+#pragma unroll
+    for (int u = 0; u < DH / 64; ++u) v[j][u] = j < ns ? po[j * DH + lane + 64 * u] : 0.f;
+  }
+  float M = m[0];
+#pragma unroll
+  for (int j = 1; j < PF_MAX_CHUNKS; ++j) M = fmaxf(M, m[j]);
+  float L = 0.f, acc[DH / 64];
+#pragma unroll
+  for (int u = 0; u < DH / 64; ++u) acc[u] = 0.f;
+#pragma unroll
+  for (int j = 0; j < PF_MAX_CHUNKS; ++j) {
+    const float wgt = __builtin_amdgcn_exp2f(m[j] - M);
+    L = fmaf(l[j], wgt, L);
+#pragma unroll
+    for (int u = 0; u < DH / 64; ++u) acc[u] = fmaf(v[j][u], wgt, acc[u]);
+  }
+  const float inv = L > 0.f ? 1.f / L : 0.f;
+#pragma unroll
+  for (int u = 0; u < DH / 64; ++u) a.o[row * DH + lane + 64 * u] = f2bf(acc[u] * inv);
 }
 
 // ------------------------------------------------------------------ launchers
@@ -1840,9 +1919,23 @@ hipError_t launch_attn_mfma_decode(const triroute_cfg &cfg, const CacheView &cv,
   return hipGetLastError();
 }
 
+// Chunks of a block's key range, for `blocks` blocks of that mode over at
+// most `keys` keys: enough for PF_FILL two-wave blocks (four a CU) when a
+// routed mix gives the mode a third of the query tiles, each chunk of at
+// least PF_KEYS_MIN keys.  Measured on whole layers: 1.3B, 2 x 1000 tokens
+// behind 7001: 1240 us unsplit, 849-855 us with PF_FILL 512, 816-821 us with
+// 1024 and 2048; 410M, 64 tokens behind 8000: 453 -> 166 us; 160M, 8 x 256
+// tokens: 203 us unsplit and with 256 keys a chunk, 211 us with 128.
+constexpr int PF_FILL = 1024, PF_KEYS_MIN = 256;
+static int pf_chunks(int blocks, int keys, int most) {
+  const int want = (3 * PF_FILL + blocks - 1) / blocks;
+  return max(1, min(min(want, keys / PF_KEYS_MIN), most));
+}
+
 hipError_t launch_attn_mfma_prefill(const triroute_cfg &cfg, const CacheView &cv, int B, int T,
-                                    const int32_t *seq_ids, const void *q,
-                                    const triroute_compaction &c, void *o, hipStream_t st) {
+                                    const int32_t *seq_ids, const void *q, const uint8_t *mode,
+                                    const triroute_compaction &c, void *o, float *part,
+                                    size_t part_bytes, hipStream_t st) {
   PrefillArgs a;
   a.cv = cv;
   a.q = (const bf16 *)q;
@@ -1850,6 +1943,7 @@ hipError_t launch_attn_mfma_prefill(const triroute_cfg &cfg, const CacheView &cv
   a.cnt = c.attn_cnt;
   a.idx = c.attn_idx;
   a.o = (bf16 *)o;
+  a.part = part;
   a.B = B;
   a.T = T;
   a.H = cfg.n_heads;
@@ -1859,19 +1953,30 @@ hipError_t launch_attn_mfma_prefill(const triroute_cfg &cfg, const CacheView &cv
   a.Hkv = cfg.n_kv_heads;
   a.NQ = (a.R + PF_WAVES * PF_HEADS - 1) / (PF_WAVES * PF_HEADS);
   a.scale2 = LOG2E / sqrtf(float(cfg.head_dim));
-  const int64_t blocks = int64_t(B) * a.Hkv * a.NQ * 2 * a.QT;
-  const dim3 grid{unsigned(blocks)};
+  const int64_t rows = int64_t(B) * T * cfg.n_heads;
+  const int64_t blocks = int64_t(B) * a.Hkv * a.NQ * a.QT;
+  // (the caller's scratch bounds the partials)
+  const int most = part ? int(min(int64_t(PF_MAX_CHUNKS),
+                                  int64_t(part_bytes) / (rows * (cfg.head_dim + 2) * 4))) : 1;
+  const int nb = int(min(blocks, int64_t(1) << 20));
+  a.nsf = pf_chunks(nb, cv.capacity, most);
+  a.nsl = pf_chunks(nb, min(cv.capacity, cfg.window), most);
+  a.NS = max(a.nsf, a.nsl);
+  const dim3 grid{unsigned(blocks * (a.nsf + a.nsl))};
+  const dim3 cgrid{unsigned((rows + 3) / 4)};
   const int G = cfg.kv_group;
   if (cfg.head_dim == 64) {
     if (G == 64)
       attn_prefill_mfma_kernel<64, 64><<<grid, 64 * PF_WAVES, 0, st>>>(a);
     else
       attn_prefill_mfma_kernel<64, 32><<<grid, 64 * PF_WAVES, 0, st>>>(a);
+    if (a.NS > 1) attn_prefill_combine_kernel<64><<<cgrid, 256, 0, st>>>(a, mode);
   } else {
     if (G == 64)
       attn_prefill_mfma_kernel<128, 64><<<grid, 64 * PF_WAVES, 0, st>>>(a);
     else
       attn_prefill_mfma_kernel<128, 32><<<grid, 64 * PF_WAVES, 0, st>>>(a);
+    if (a.NS > 1) attn_prefill_combine_kernel<128><<<cgrid, 256, 0, st>>>(a, mode);
   }
   return hipGetLastError();
 }

@@ -110,9 +110,11 @@ size_t decode_part_floats(const triroute_cfg &cfg, int B);
 hipError_t launch_attn_mfma_decode(const triroute_cfg &cfg, const CacheView &cv, int B,
                                    const int32_t *seq_ids, const void *q, const uint8_t *mode,
                                    void *o, float *part, hipStream_t st);
+// part, part_bytes: scratch for the chunks of split key ranges (may be NULL: no split)
 hipError_t launch_attn_mfma_prefill(const triroute_cfg &cfg, const CacheView &cv, int B, int T,
-                                    const int32_t *seq_ids, const void *q,
-                                    const triroute_compaction &c, void *o, hipStream_t st);
+                                    const int32_t *seq_ids, const void *q, const uint8_t *mode,
+                                    const triroute_compaction &c, void *o, float *part,
+                                    size_t part_bytes, hipStream_t st);
 // misc.hip
 hipError_t launch_moe_norm_rows(const triroute_cfg &cfg, int N, const void *x, const void *g,
                                 const triroute_compaction &c, const int32_t *eidx, void *out,
