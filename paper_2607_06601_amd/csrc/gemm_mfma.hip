@@ -1,10 +1,10 @@
 // bf16 GEMMs of the layer on gfx950 MFMA: C = A B^T, both operands
 // K-contiguous, fp32 accumulation (v_mfma_f32_16x16x32_bf16).
 //
-// Block tile BM x BN, K step 64, 8 waves arranged WM x WN, each wave owning a
-// (BM/WM) x 64 sub-tile.  A and B tiles are double-buffered in LDS (rows of
-// 128 B, 16-byte chunk c of row r stored at c ^ (r & 7)); the next K step is
-// fetched into registers while the current one feeds the MFMAs.
+// Two kernels: gemm_mfma_kernel, BM x BN tiles on WM x WN waves with S operand
+// stages in LDS, for few and middling rows, and the persistent four-wave
+// gemm_w4_kernel for many.  The launchers choose the tile by the rounds it
+// makes over the CUs.
 //
 // Epilogues work on the accumulator registers.  Within a wave's 64 columns
 // the B rows are ordered so that column j of 16-column block ni and block
@@ -773,7 +773,7 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_mfma_kernel(P p, int K, 
 
 // ------------------------------------------------------- four-wave kernel
 // One wave per SIMD, each wave a (BM/2) x (BN/2) sub-tile: every operand byte
-// read from LDS feeds twice the MFMAs of the eight-wave kernel above (per K
+// read from LDS feeds twice the MFMAs of a 128 x 64 wave tile (per K
 // step and CU, 128 KB of fragment reads against 256 MFMAs per SIMD).  With
 // no second wave on its SIMD to switch to, a wave hides LDS latency itself:
 // the fragments of the next 32-wide K slice are read into a second register
@@ -870,7 +870,7 @@ __global__ __launch_bounds__(256, 1) void gemm_w4_kernel(P p, int K, int ny) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform, in SGPRs
   const int wm = wave / WN, wn = wave % WN;
   // Transfer j of this wave fills stage rows RPT (wave IPW + j) .. + RPT - 1
-  // as in the eight-wave kernel.  A transfer's rows are all A rows or all B
+  // as in the kernel above.  A transfer's rows are all A rows or all B
   // rows (RPT divides BM), so each lane keeps one 32-bit byte offset per
   // transfer from that operand's base (the host checks that every operand
   // row lies within 4 GB of it); the base moves on by 128 B per K step.
@@ -1070,6 +1070,53 @@ static bool span32(std::initializer_list<Span> ms, const bf16 **lo) {
   return b - a < (uintptr_t(1) << 32);
 }
 
+// Choice of the tile of a product of N rows and c128 columns of 128.  A tile
+// shape costs its rounds over the CUs (slots of a round: blocks resident at
+// once) times the time of one round, relative to the 128 x 128 tile's with
+// two blocks of four waves a CU (40 us at K 2048, 22 us at K 1024):
+//   128 x 128, eight waves, three stages, one block a CU  0.65, one round only
+//   64 x 128, two stages, three blocks a CU               0.9
+//   256 x 128 / 192 / 256, four waves, one block a CU     0.95 / 1.15 / 1.3
+// The large tiles win where they fill their rounds, the small ones in
+// between.  Measured (us; weights not in a cache; before: the 32-row tiles up
+// to 2048 tokens and the four-wave kernel above): 1.3B QKV 700 tokens 39 -> 26,
+// 1000 44 -> 27, 2000 87 -> 42, 2500 56 -> 44; 410M QKV 2500 22 -> 18, 6000
+// 41 -> 34; 160M QKV 8192 36 -> 29; 1.3B O-projection 2000 57 -> 24, 4096 50 -> 40;
+// 410M 2500 25 -> 13, 4096 27 -> 14; 160M 4096 18 -> 11; the full batches
+// (16384) keep the four-wave tiles, but for 160M QKV (51 -> 48).
+constexpr float COST_ONE_ROUND = 0.65f, COST_64X128 = 0.9f, COST_128X128 = 1.f,
+                COST_256X128 = 0.95f, COST_256X192 = 1.15f, COST_256X256 = 1.3f;
+static float tile_cost(int tiles, float cost, int per_cu = 1) {
+  const int slots = cu_count() * per_cu;
+  return float((tiles + slots - 1) / slots) * cost;
+}
+static int tiles64(int N, int c128) { return (N + 63) / 64 * c128; }
+static int tiles128(int N, int c128) { return (N + 127) / 128 * c128; }
+static bool one_round(int t128) { return t128 <= cu_count(); }
+// the four-wave kernel's rounds, at cost t, beat the smaller tiles'
+static bool w4_rounds(int N, int c128, float t) {
+  if (one_round(tiles128(N, c128))) return t <= COST_ONE_ROUND;
+  return t <= std::min(tile_cost(tiles64(N, c128), COST_64X128, 3),
+                       tile_cost(tiles128(N, c128), COST_128X128, 2));
+}
+// Below 192 tiles of 64 x 128 most CUs would have none: the 32-row tiles
+// stream the weights from more of them (410M QKV 512 tokens, 96 tiles: 12.4
+// against 13.9 us; 1.3B QKV 512 tokens, 192 tiles: 29.5 against 23.5 us).
+static bool few_tiles(int N, int c128) { return tiles64(N, c128) < 192; }
+
+// Up to 288 tiles of 64 rows, three stages: the blocks wait on each step's
+// transfers (1.3B O-projection, 1000 tokens, 256 tiles: 19.2 us, with two
+// stages 29.3, the 128-row tiles 22.2).
+template <class P>
+static hipError_t launch_mid(const P &p, int K, int N, int c128, hipStream_t st) {
+  const int m64 = (N + 63) / 64, m128 = (N + 127) / 128;
+  if (tiles64(N, c128) <= 288) return launch<P, 64, 128, 2, 2, 64, 3>(p, K, m64, c128, st);
+  if (one_round(m128 * c128)) return launch<P, 128, 128, 4, 2, 64, 3>(p, K, m128, c128, st);
+  if (tile_cost(m64 * c128, COST_64X128, 3) <= tile_cost(m128 * c128, COST_128X128, 2))
+    return launch<P, 64, 128, 2, 2, 64, 2>(p, K, m64, c128, st);
+  return launch<P, 128, 128, 2, 2, 64, 2>(p, K, m128, c128, st);
+}
+
 hipError_t mfma_qkv(const triroute_cfg &cfg, int B, int Tq, const void *n1,
                     const triroute_dense_w &w, const float *rope, void *q, void *k, void *v,
                     hipStream_t st) {
@@ -1089,34 +1136,36 @@ hipError_t mfma_qkv(const triroute_cfg &cfg, int B, int Tq, const void *n1,
   p.Hkv = cfg.n_kv_heads;
   p.dh = cfg.head_dim;
   p.Ncols = (cfg.n_heads + 2 * cfg.n_kv_heads) * cfg.head_dim;
+  const int c128 = (p.Ncols + 127) / 128;
   // Few tokens (decode): the product streams the weights; 32-row tiles one
   // head wide put one block on every head and row tile.
-  if (p.N <= 2048) {
+  if (few_tiles(p.N, c128)) {
     if (p.dh == 64)
       return launch<QkvM, 32, 64, 2, 1, 64, 4>(p, cfg.d_model, (p.N + 31) / 32, (p.Ncols + 63) / 64, st);
-    if (p.dh == 128)
-      return launch<QkvM, 32, 128, 2, 2, 64, 4>(p, cfg.d_model, (p.N + 31) / 32, (p.Ncols + 127) / 128, st);
+    return launch<QkvM, 32, 128, 2, 2, 64, 4>(p, cfg.d_model, (p.N + 31) / 32, c128, st);
   }
   const bf16 *lo;
-  const bool w4 = (p.dh == 64 || p.dh == 128) && p.Ncols % 128 == 0 && p.d >= 128 &&
+  const bool w4 = p.Ncols % 128 == 0 && p.d >= 128 &&
                   span32({{p.Wq, size_t(p.H) * p.dh * p.d * sizeof(bf16)},
                           {p.Wk, size_t(p.Hkv) * p.dh * p.d * sizeof(bf16)},
                           {p.Wv, size_t(p.Hkv) * p.dh * p.d * sizeof(bf16)}}, &lo) &&
                   span32({{p.n1, size_t(p.N) * p.d * sizeof(bf16)}}, &lo);
-  if (w4) {
+  // d_h 128: one head per wave column on 256-column tiles (long K steps),
+  // where the columns divide into them
+  const bool wide = p.dh == 128 && p.Ncols % 256 == 0;
+  const int mt = (p.N + 255) / 256;
+  if (w4 && w4_rounds(p.N, c128, wide ? tile_cost(mt * (p.Ncols / 256), COST_256X256)
+                                      : tile_cost(mt * c128, COST_256X128))) {
     const uint32_t pitch = 2u * uint32_t(p.d);
     p.Hd = p.H * p.dh;
     p.HKd = p.Hd + p.Hkv * p.dh;
     p.wq_o = uint32_t((const uint8_t *)p.Wq - (const uint8_t *)p.Wlo);
     p.wk_o = uint32_t((const uint8_t *)p.Wk - (const uint8_t *)p.Wlo) - uint32_t(p.Hd) * pitch;
     p.wv_o = uint32_t((const uint8_t *)p.Wv - (const uint8_t *)p.Wlo) - uint32_t(p.HKd) * pitch;
-    // d_h 128: one head per wave column on 256-column tiles (long K steps,
-    // one barrier each), where the columns divide into them
-    if (p.dh == 128 && p.Ncols % 256 == 0)
-      return launch_w4<QkvM, 256, 256>(p, cfg.d_model, (p.N + 255) / 256, p.Ncols / 256, st);
-    return launch_w4<QkvM, 256, 128>(p, cfg.d_model, (p.N + 255) / 256, p.Ncols / 128, st);
+    if (wide) return launch_w4<QkvM, 256, 256>(p, cfg.d_model, mt, p.Ncols / 256, st);
+    return launch_w4<QkvM, 256, 128>(p, cfg.d_model, mt, c128, st);
   }
-  return launch<QkvM, 256, 128, 4, 2, 64, 3>(p, cfg.d_model, (p.N + 255) / 256, (p.Ncols + 127) / 128, st);
+  return launch_mid(p, cfg.d_model, p.N, c128, st);
 }
 
 hipError_t mfma_oproj(const triroute_cfg &cfg, int N, const void *x, const void *o,
@@ -1129,20 +1178,22 @@ hipError_t mfma_oproj(const triroute_cfg &cfg, int N, const void *x, const void 
   p.N = N;
   p.d = cfg.d_model;
   p.K = cfg.n_heads * cfg.head_dim;
-  const bf16 *lo;
-  if (N <= 2048)  // few tokens: weight streaming, narrow tiles as for QKV
+  const int c128 = (p.d + 127) / 128;
+  if (few_tiles(N, c128))  // few tokens: weight streaming, narrow tiles as for QKV
     return launch<OprojM, 32, 64, 2, 1, 64, 4>(p, p.K, (N + 31) / 32, (p.d + 63) / 64, st);
+  const bf16 *lo;
   const bool w4 = p.K >= 128 && span32({{p.o, size_t(N) * p.K * sizeof(bf16)}}, &lo) &&
                   span32({{p.Wo, size_t(p.d) * p.K * sizeof(bf16)}}, &lo);
-  if (w4) {  // 192- or 256-wide tiles: whichever fills the CUs in fewer rounds of shorter steps
-    const int mt = (N + 255) / 256, cu = cu_count();
-    const int r192 = p.d % 192 == 0 ? (mt * (p.d / 192) + cu - 1) / cu : 0;
-    const int r256 = p.d % 256 == 0 ? (mt * (p.d / 256) + cu - 1) / cu : 0;
-    if (r192 > 0 && (r256 == 0 || 3 * r192 <= 4 * r256))
-      return launch_w4<OprojM, 256, 192>(p, p.K, mt, p.d / 192, st);
-    if (r256 > 0) return launch_w4<OprojM, 256, 256>(p, p.K, mt, p.d / 256, st);
+  if (w4) {
+    const int mt = (N + 255) / 256;
+    const float t192 = p.d % 192 == 0 ? tile_cost(mt * (p.d / 192), COST_256X192) : 1e30f;
+    const float t256 = p.d % 256 == 0 ? tile_cost(mt * (p.d / 256), COST_256X256) : 1e30f;
+    if (w4_rounds(N, c128, std::min(t192, t256))) {
+      if (t192 <= t256) return launch_w4<OprojM, 256, 192>(p, p.K, mt, p.d / 192, st);
+      return launch_w4<OprojM, 256, 256>(p, p.K, mt, p.d / 256, st);
+    }
   }
-  return launch<OprojM, 256, 128, 4, 2, 64, 3>(p, p.K, (N + 255) / 256, (p.d + 127) / 128, st);
+  return launch_mid(p, p.K, N, c128, st);
 }
 
 hipError_t mfma_moe(const triroute_cfg &cfg, int N, const void *n2, const triroute_moe_w &w,
@@ -1160,16 +1211,36 @@ hipError_t mfma_moe(const triroute_cfg &cfg, int N, const void *n2, const trirou
   p1.dff = dff;
   const size_t wb = size_t(E) * dff * d * sizeof(bf16);
   const bf16 *alo;
-  // Few assignments (decode): each expert's rows fit a 32-row tile and the
-  // work is streaming the expert weights, so narrow 32 x 64 tiles (two
-  // waves, four stages) put every CU on its own slice of the weights.
-  const bool small = Nk <= 2048;
-  const bool w4 = span32({{p1.Wg, wb}, {p1.Wu, wb}}, &p1.Wlo) &&
+  // Rows an expert has when the router spreads its options evenly, and the
+  // tiles of BM rows that E such experts make (a few rows more, as the
+  // counts vary).
+  const int r = Nk / (E + 1);
+  auto row_tiles = [&](int BM) { return E * ((r + r / 32 + BM) / BM); };
+  // Gate/up.  Up to 24 rows an expert the work is streaming the expert
+  // weights: narrow 32 x 64 tiles (two waves, four stages) put every CU on
+  // its own slice of them.  Up to 64 rows one 64-row tile reads each weight
+  // once (the 32-row tiles read it per row tile).  Above, 128 x 128 tiles if
+  // they make one round, else the four-wave kernel with 128- or 256-row
+  // tiles, whichever needs less time for its rounds (a 256-row tile takes
+  // 1.77 times a 128-row one).  Gate/up alone within the expert block (us;
+  // weights not in a cache; before: 32-row tiles up to 2048 assignments,
+  // 256-row tiles above): the block on 410M at 200 tokens 57 -> 49, 400
+  // 82 -> 62, 700 118 -> 82, 2000 136 -> 133; 1.3B 400 402 -> 282, 700
+  // 598 -> 351, 1000 789 -> 419; 160M 400 53 -> 40, 700 72 -> 53.
+  const bool w4 = d >= 128 && span32({{p1.Wg, wb}, {p1.Wu, wb}}, &p1.Wlo) &&
                   span32({{p1.n2, size_t(Nk) * d * sizeof(bf16)}}, &alo);
-  hipError_t err =
-      small ? launch<Moe1M, 32, 64, 2, 1, 64, 4>(p1, d, Nk / 32 + E, (dff + 31) / 32, st)
-      : w4 && d >= 128 ? launch_w4<Moe1M, 256, 256>(p1, d, Nk / 256 + E, (dff + 127) / 128, st)
-            : launch<Moe1M, 256, 256, 2, 4, 64, 2>(p1, d, Nk / 256 + E, (dff + 127) / 128, st);
+  const int ny = (dff + 127) / 128;
+  hipError_t err;
+  if (r <= 24)
+    err = launch<Moe1M, 32, 64, 2, 1, 64, 4>(p1, d, Nk / 32 + E, (dff + 31) / 32, st);
+  else if (r <= 64)
+    err = launch<Moe1M, 64, 128, 2, 2, 64, 3>(p1, d, Nk / 64 + E, (dff + 63) / 64, st);
+  else if (!w4 || one_round(row_tiles(128) * ((dff + 63) / 64)))
+    err = launch<Moe1M, 128, 128, 4, 2, 64, 3>(p1, d, Nk / 128 + E, (dff + 63) / 64, st);
+  else if (tile_cost(row_tiles(128) * ny, 1.f) < tile_cost(row_tiles(256) * ny, 1.77f))
+    err = launch_w4<Moe1M, 128, 256>(p1, d, Nk / 128 + E, ny, st);
+  else
+    err = launch_w4<Moe1M, 256, 256>(p1, d, Nk / 256 + E, ny, st);
   if (err != hipSuccess) return err;
   Moe2M p2;
   p2.Hm = (const bf16 *)Hm;
@@ -1179,20 +1250,39 @@ hipError_t mfma_moe(const triroute_cfg &cfg, int N, const void *n2, const trirou
   p2.E = E;
   p2.d = d;
   p2.dff = dff;
-  if (small) {
+  // Down.  Up to 2048 assignments K is split in halves, each with its plane
+  // of Y (moe_ysplit); 64- or 128-row tiles where they fill the CUs or the
+  // rows fill them, else the 32-row tiles (down alone within the block, us:
+  // 1.3B 400 tokens 402 -> 361, 700 598 -> 508; 410M 400 82 -> 75, 1000 154 -> 135;
+  // 410M 100, 16 rows an expert: 32-row tiles 41.5, 64-row 45.8).
+  const int c128 = (d + 127) / 128;
+  if (Nk <= 2048) {
     p2.ksplit = moe_ysplit(cfg, N);
     p2.yplane = int64_t(Nk) * d;
-    return launch<Moe2M, 32, 64, 2, 1, 64, 4>(p2, dff / p2.ksplit, Nk / 32 + E,
-                                              (d + 63) / 64 * p2.ksplit, st);
+    const int K = dff / p2.ksplit, cols = c128 * p2.ksplit;
+    if (r > 64 && row_tiles(128) * cols >= 256)
+      return launch<Moe2M, 128, 128, 4, 2, 64, 3>(p2, K, Nk / 128 + E, cols, st);
+    if (r > 64) return launch<Moe2M, 64, 128, 2, 2, 64, 3>(p2, K, Nk / 64 + E, cols, st);
+    if (row_tiles(64) * cols >= 256)
+      return launch<Moe2M, 64, 128, 2, 2, 64, 2>(p2, K, Nk / 64 + E, cols, st);
+    return launch<Moe2M, 32, 64, 2, 1, 64, 4>(p2, K, Nk / 32 + E, (d + 63) / 64 * p2.ksplit, st);
   }
+  // Above: 128 x 128 tiles if they make one round (410M, 2000 tokens: the
+  // block 136 -> 106 us), else the four-wave kernel, with 256-row tiles where
+  // one holds an expert's rows (each weight is read once: 1.3B, 2000 tokens,
+  // 360 us, 128-row tiles 371) or their rounds are cheaper (192-wide ones
+  // where they divide d), else 128-row ones (410M, 3000 tokens: 165 -> 150).
   const bool w4b = dff >= 128 && (d % 192 == 0 || d % 256 == 0) && span32({{p2.Wd, wb}}, &alo) &&
                    span32({{p2.Hm, size_t(Nk) * dff * sizeof(bf16)}}, &alo);
-  if (w4b) {  // 192-wide tiles where they divide d (measured faster), else 256
-    const int mt = Nk / 256 + E;
-    if (d % 192 == 0) return launch_w4<Moe2M, 256, 192>(p2, dff, mt, d / 192, st);
-    return launch_w4<Moe2M, 256, 256>(p2, dff, mt, d / 256, st);
-  }
-  return launch<Moe2M, 256, 128, 4, 2, 64, 3>(p2, dff, Nk / 256 + E, (d + 127) / 128, st);
+  if (!w4b || one_round(row_tiles(128) * c128))
+    return launch<Moe2M, 128, 128, 4, 2, 64, 3>(p2, dff, Nk / 128 + E, c128, st);
+  const bool by192 = d % 192 == 0;
+  const float t128 = tile_cost(row_tiles(128) * (d / 256), 1.f);
+  const float t256 = tile_cost(row_tiles(256) * (by192 ? d / 192 : d / 256), by192 ? 1.5f : 1.77f);
+  if (d % 256 == 0 && row_tiles(256) > E && t128 < t256)
+    return launch_w4<Moe2M, 128, 256>(p2, dff, Nk / 128 + E, d / 256, st);
+  if (by192) return launch_w4<Moe2M, 256, 192>(p2, dff, Nk / 256 + E, d / 192, st);
+  return launch_w4<Moe2M, 256, 256>(p2, dff, Nk / 256 + E, d / 256, st);
 }
 
 }  // namespace tr

@@ -9,7 +9,7 @@ import oracle
 import paper_2607_06601_amd as tr
 from paper_2607_06601_amd.device import DeviceLayer, to_dev
 
-from _common import assert_close, npy, torch_act
+from _common import assert_close, bound_of, note, npy, torch_act
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -126,3 +126,118 @@ def test_prefill_split_key_ranges(monkeypatch, B, T, H, Hkv, dh, w, ctx, pages):
     assert_close(npy(t["o"]), npy(o), "bf16", "o (split against unsplit)")
     if B > 2:
         assert not npy(t["o"]).reshape(B, -1)[1].any()
+
+
+# ------------------------------------------------------- GEMM tile choices
+@pytest.mark.parametrize("H,Hkv,dh,d,n_tok", [
+    (4, 1, 64, 256, 4032), (4, 1, 64, 256, 4033),      # 32-row tiles to 64 x 128 (3 columns of 128)
+    (3, 1, 64, 192, 6200),                             # 320 columns: the last tile half empty
+    (16, 4, 128, 128, 768), (16, 4, 128, 128, 769),    # 288 tiles of 64 rows; 128 x 128, one round
+    (16, 4, 128, 128, 1280), (16, 4, 128, 128, 1281),  # its last; 64 x 128, three blocks a CU
+    (16, 4, 128, 128, 2049), (16, 4, 128, 128, 2700),  # 128 x 128, two a CU; 256 x 256, four waves
+    (16, 8, 64, 128, 4000),                            # 256 x 128, four waves
+])
+def test_projection_tiles(H, Hkv, dh, d, n_tok):
+    """QKV and the O-projection on both sides of their tile choices, against
+    plain fp32 products of the same bf16 operands."""
+    c = tr.make_cfg(d, H, Hkv, dh, 64, 4, 1, 512, 64, "bf16")
+    g = torch.Generator(device=DEV)
+    g.manual_seed(51)
+
+    def rnd(*shape, std=1.0):
+        return (torch.randn(shape, generator=g, device=DEV) * std).bfloat16()
+
+    nq, nkv = H * dh, Hkv * dh
+    w, wo, n1, x = rnd(nq + 2 * nkv, d, std=d ** -0.5), rnd(d, nq, std=nq ** -0.5), rnd(n_tok, d), \
+        rnd(n_tok, d)
+    dw = tr.DenseW(Wq=w.data_ptr(), Wk=w[nq:].data_ptr(), Wv=w[nq + nkv:].data_ptr(),
+                   Wo=wo.data_ptr())
+    out = {n: torch.full((n_tok, m), float("nan"), dtype=torch.bfloat16, device=DEV)
+           for n, m in (("q", nq), ("k", nkv), ("v", nkv))}
+    xt = torch.full((n_tok, d), float("nan"), dtype=torch.bfloat16, device=DEV)
+    print(f"projections H={H}/{Hkv} dh={dh} d={d} n={n_tok}", flush=True)
+    tr.qkv(c, 1, n_tok, n1, dw, out["q"], out["k"], out["v"],
+           tr.workspace(c, tr.OP_QKV, 1, n_tok))
+    tr.oproj(c, n_tok, x, out["q"], dw, xt)
+    torch.cuda.synchronize()
+    y = n1.float() @ w.float().t()
+    half = dh // 2
+    inv = 1e4 ** (-2.0 * torch.arange(half, dtype=torch.float64, device=DEV) / dh)
+    ang = torch.arange(n_tok, dtype=torch.float64, device=DEV)[:, None, None] * inv
+    cs, sn = ang.cos().float(), ang.sin().float()
+
+    def rope(t):
+        t = t.reshape(n_tok, -1, dh)
+        a, b = t[..., :half], t[..., half:]
+        return torch.cat([a * cs - b * sn, a * sn + b * cs], -1).reshape(n_tok, -1)
+
+    ref = dict(q=rope(y[:, :nq]), k=rope(y[:, nq:nq + nkv]), v=y[:, nq + nkv:])
+    for n, t in out.items():
+        assert_close(npy(t), npy(ref[n]), "bf16", n)
+    assert_close(npy(xt), npy(x.float() + out["q"].float() @ wo.float().t()), "bf16", "xt")
+
+
+@pytest.mark.parametrize("E,k,d,dff,n_tok,skew", [
+    (4, 1, 256, 512, 124, 0), (4, 1, 256, 512, 125, 0),   # 24 rows an expert and one more
+    (4, 1, 256, 512, 324, 0), (4, 1, 256, 512, 325, 0),   # 64 and 65
+    (16, 2, 1024, 256, 300, 0),                           # down: 64 x 128 over K halves
+    (4, 2, 2048, 256, 700, 0),                            # down: 128 x 128 over K halves
+    (8, 2, 256, 4096, 900, 0),                            # gate/up: four waves, 128 rows
+    (4, 2, 256, 512, 1024, 0), (4, 2, 256, 512, 1025, 0), # K halves end; 128 x 128 down tiles
+    (8, 2, 1024, 2048, 3000, 0),                          # 128-row four-wave tiles in both
+    (8, 2, 768, 320, 3001, 0),                            # d a multiple of 192 and 256
+    (16, 2, 2048, 192, 2000, 0),                          # one 256-row tile an expert
+    (3, 2, 192, 192, 4000, 0), (3, 2, 192, 192, 40000, 0),  # 192-wide columns only
+    (2, 1, 64, 64, 3000, 0),                              # K too short for the four-wave kernel
+    (8, 2, 512, 384, 2100, 1), (8, 2, 512, 384, 150, 1),  # one expert takes nearly all rows
+])
+def test_expert_tiles(E, k, d, dff, n_tok, skew):
+    """The expert block on both sides of its tile choices, against fp32 torch
+    (n2 and the SwiGLU product held in bf16, as the layer's contract has them)."""
+    c = tr.make_cfg(d, 4, 1, 64, 64, E, k, dff, 64, "bf16")
+    g = torch.Generator(device=DEV)
+    g.manual_seed(52)
+
+    def rnd(*shape, std=1.0):
+        return (torch.randn(shape, generator=g, device=DEV) * std).bfloat16()
+
+    xt, g2 = rnd(n_tok, d), rnd(d, std=0.02) + 1
+    wg, wu, wd = rnd(E, dff, d, std=d ** -0.5), rnd(E, dff, d, std=d ** -0.5), rnd(E, d, dff,
+                                                                                  std=dff ** -0.5)
+    z = torch.randn(n_tok, E + 1, generator=g, device=DEV)
+    if skew:
+        z[:, 2] += 6
+    eidx = z.topk(k).indices.sort(1).values
+    gate = torch.softmax(torch.randn(n_tok, k, generator=g, device=DEV), 1)
+    cmp = tr.CompactionBuffers(c, 1, n_tok)
+    cnt = torch.bincount(eidx.reshape(-1), minlength=E + 1)
+    cmp.exp_cnt.copy_(cnt)
+    cmp.exp_off[1:].copy_(cnt[1:].cumsum(0))
+    cmp.exp_rows[:n_tok * k - int(cnt[0])].copy_(
+        eidx.reshape(-1).argsort(stable=True)[int(cnt[0]):])
+    x_out = torch.full_like(xt, float("nan"))
+    ws = tr.workspace(c, tr.OP_MOE, n_tok, 1)
+    ws.fill_(0xFF)
+    print(f"experts E={E} k={k} d={d} dff={dff} n={n_tok}", flush=True)
+    tr.moe(c, n_tok, xt, tr.DenseW(g2=g2.data_ptr()),
+           tr.MoeW(wg.data_ptr(), wu.data_ptr(), wd.data_ptr()), eidx.int().contiguous(), gate,
+           cmp.struct, x_out, ws)
+    torch.cuda.synchronize()
+    xd = xt.double()
+    n2 = (xd * torch.rsqrt(xd.square().mean(1, keepdim=True) + 1e-6) * g2.double()).bfloat16()
+    ref, flip = xt.float().clone(), torch.zeros(n_tok, device=DEV)
+    for e in range(1, E + 1):
+        rows, slot = (eidx == e).nonzero(as_tuple=True)
+        u = n2[rows].float()
+        h = torch.nn.functional.silu(u @ wg[e - 1].float().t()) * (u @ wu[e - 1].float().t())
+        ref.index_add_(0, rows, (h.bfloat16().float() @ wd[e - 1].float().t())
+                       * gate[rows, slot][:, None])
+        # the two sides' fp32 sums differ in their last bits, and where that
+        # moves an element of H to the next bf16 value (2^-8 of it at most)
+        # the row's outputs move by that much times a weight and the gate;
+        # more than one of the largest elements of a row does not
+        flip.index_add_(0, rows, h.abs().amax(1) * gate[rows, slot] * wd[e - 1].abs().amax() / 256)
+    err = np.abs(npy(x_out).astype(np.float64) - npy(ref))
+    ratio = float((err / (bound_of(npy(ref), "bf16") + npy(flip)[:, None])).max())
+    note("x_out (one H step allowed)", ratio)
+    assert ratio <= 1.0, ratio
