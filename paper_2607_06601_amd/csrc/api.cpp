@@ -449,7 +449,7 @@ hipError_t run_attn_prefill(const triroute_cfg &c, const triroute_kv_cache &kc, 
   const tr::CacheView v = tr::make_view(c, kc);
   return c.act == TRIROUTE_BF16 ? tr::launch_attn_mfma_prefill(c, v, B, T, seq_ids, q, mode, cmp, o, part,
                                                                  part_bytes, st)
-                                : tr::launch_attn_valu_prefill(c, v, B, T, seq_ids, q, cmp, o, st);
+                                : tr::launch_attn_f32_prefill(c, v, B, T, seq_ids, q, cmp, o, st);
 }
 
 hipError_t run_attn_decode(const triroute_cfg &c, const triroute_kv_cache &kc, int B,
@@ -457,7 +457,7 @@ hipError_t run_attn_decode(const triroute_cfg &c, const triroute_kv_cache &kc, i
                            float *part, hipStream_t st) {
   const tr::CacheView v = tr::make_view(c, kc);
   return c.act == TRIROUTE_BF16 ? tr::launch_attn_mfma_decode(c, v, B, seq_ids, q, mode, o, part, st)
-                                : tr::launch_attn_valu_decode(c, v, B, seq_ids, q, mode, o, st);
+                                : tr::launch_attn_f32_decode(c, v, B, seq_ids, q, mode, o, st);
 }
 
 }  // namespace

@@ -2,6 +2,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <limits.h>
 #include <stdint.h>
 
 #include "triroute.h"
@@ -247,6 +248,54 @@ struct CacheView {
     return 1024 * bits(bi) + TS * (dh / G) * 4;
   }
 };
+
+// Lower bounds, in the sorted key positions of pool k % 4 of sequence s, of
+// key[k] for eight (pool, key) pairs at once: each round probes 64 evenly
+// spaced entries of every range still longer than 64, the eight loads in
+// flight together.  A key <= 0 has bound 0 (positions are >= 0).  Called by
+// the whole wave with wave-uniform arguments.
+__device__ __forceinline__ void lower_bounds8(const CacheView &cv, int s, const int *len,
+                                              const int *key, int *res) {
+  const int lane = threadIdx.x & 63;
+  int lo[8], hi[8];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    lo[k] = 0;
+    hi[k] = key[k] <= 0 ? 0 : len[k & 3];
+  }
+  for (;;) {
+    bool more = false;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) more |= hi[k] - lo[k] > 64;
+    if (!more) break;
+    int v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const int span = hi[k] - lo[k];
+      v[k] = 0;
+      if (span > 64) v[k] = cv.pos_at(s, k & 3, lo[k] + int(int64_t(span) * (lane + 1) / 64) - 1);
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const int span = hi[k] - lo[k];
+      if (span > 64) {
+        const int c = __popcll(__ballot(v[k] < key[k]));  // probes 0 .. c-1 lie below the key
+        const int nlo = c > 0 ? lo[k] + int(int64_t(span) * c / 64) : lo[k];
+        const int nhi = c < 64 ? lo[k] + int(int64_t(span) * (c + 1) / 64) - 1 : hi[k];
+        lo[k] = nlo;
+        hi[k] = nhi;
+      }
+    }
+  }
+  int v[8];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const int idx = lo[k] + lane;
+    v[k] = idx < hi[k] ? cv.pos_at(s, k & 3, idx) : INT_MAX;
+  }
+#pragma unroll
+  for (int k = 0; k < 8; ++k) res[k] = lo[k] + __popcll(__ballot(v[k] < key[k]));
+}
 
 // Element placement inside a 64-lane record (see triroute.h).
 // K element (slot st in tile, channel c) -> (lane record, element index q).

@@ -96,11 +96,11 @@ hipError_t mfma_oproj(const triroute_cfg &cfg, int N, const void *x, const void 
                       const triroute_dense_w &w, void *xt, hipStream_t st);
 hipError_t mfma_moe(const triroute_cfg &cfg, int N, const void *n2, const triroute_moe_w &w,
                     const triroute_compaction &c, void *Hm, float *Y, hipStream_t st);
-// attn_valu.hip
-hipError_t launch_attn_valu_prefill(const triroute_cfg &cfg, const CacheView &cv, int B, int Tq,
+// attn_f32.hip
+hipError_t launch_attn_f32_prefill(const triroute_cfg &cfg, const CacheView &cv, int B, int Tq,
                                     const int32_t *seq_ids, const void *q,
                                     const triroute_compaction &c, void *o, hipStream_t st);
-hipError_t launch_attn_valu_decode(const triroute_cfg &cfg, const CacheView &cv, int B,
+hipError_t launch_attn_f32_decode(const triroute_cfg &cfg, const CacheView &cv, int B,
                                    const int32_t *seq_ids, const void *q, const uint8_t *mode,
                                    void *o, hipStream_t st);
 // attn_mfma.hip (bf16)

@@ -241,3 +241,113 @@ def test_expert_tiles(E, k, d, dff, n_tok, skew):
     ratio = float((err / (bound_of(npy(ref), "bf16") + npy(flip)[:, None])).max())
     note("x_out (one H step allowed)", ratio)
     assert ratio <= 1.0, ratio
+
+
+# --------------------------------------------------------------- fp32 path
+@pytest.mark.parametrize("H,Hkv,dh,d,dff,E,k,n_tok", [
+    (4, 1, 64, 64, 64, 2, 1, 1),        # K 64 split over four waves, one row
+    (2, 1, 128, 192, 320, 3, 2, 33),    # an odd number of 32-column units, a ragged row tile
+    (8, 2, 128, 512, 1024, 4, 2, 2111), # 64 x 64 tiles over all of K
+    (3, 1, 64, 448, 192, 5, 5, 2900),   # the same with an odd number of units
+])
+def test_f32_products(H, Hkv, dh, d, dff, E, k, n_tok):
+    """fp32 projections and experts against fp64 torch, within the fp32 bound
+    1e-5 (|ref| + rms(ref))."""
+    c = tr.make_cfg(d, H, Hkv, dh, 64, E, k, dff, 32, "f32")
+    g = torch.Generator(device=DEV)
+    g.manual_seed(61)
+
+    def rnd(*shape, std=1.0):
+        return torch.randn(shape, generator=g, device=DEV) * std
+
+    nq, nkv = H * dh, Hkv * dh
+    w, wo, n1, x = rnd(nq + 2 * nkv, d, std=d ** -0.5), rnd(d, nq, std=nq ** -0.5), rnd(n_tok, d), \
+        rnd(n_tok, d)
+    g2, wg, wu = rnd(d, std=0.02) + 1, rnd(E, dff, d, std=d ** -0.5), rnd(E, dff, d, std=d ** -0.5)
+    wd = rnd(E, d, dff, std=dff ** -0.5)
+    dw = tr.DenseW(Wq=w.data_ptr(), Wk=w[nq:].data_ptr(), Wv=w[nq + nkv:].data_ptr(),
+                   Wo=wo.data_ptr(), g2=g2.data_ptr())
+    out = {n: torch.full((n_tok, m), float("nan"), device=DEV)
+           for n, m in (("q", nq), ("k", nkv), ("v", nkv), ("xt", d), ("x_out", d))}
+    print(f"f32 products d={d} n={n_tok}", flush=True)
+    tr.qkv(c, 1, n_tok, n1, dw, out["q"], out["k"], out["v"], tr.workspace(c, tr.OP_QKV, 1, n_tok))
+    tr.oproj(c, n_tok, x, out["q"], dw, out["xt"])
+    eidx = torch.randn(n_tok, E + 1, generator=g, device=DEV).topk(k).indices.sort(1).values
+    gate = torch.softmax(torch.randn(n_tok, k, generator=g, device=DEV), 1)
+    cmp = tr.CompactionBuffers(c, 1, n_tok)
+    cnt = torch.bincount(eidx.reshape(-1), minlength=E + 1)
+    cmp.exp_cnt.copy_(cnt)
+    cmp.exp_off[1:].copy_(cnt[1:].cumsum(0))
+    cmp.exp_rows[:n_tok * k - int(cnt[0])].copy_(
+        eidx.reshape(-1).argsort(stable=True)[int(cnt[0]):])
+    tr.moe(c, n_tok, x, dw, tr.MoeW(wg.data_ptr(), wu.data_ptr(), wd.data_ptr()),
+           eidx.int().contiguous(), gate, cmp.struct, out["x_out"], tr.workspace(c, tr.OP_MOE, n_tok, 1))
+    torch.cuda.synchronize()
+    y = n1.double() @ w.double().t()
+    half = dh // 2
+    inv = 1e4 ** (-2.0 * torch.arange(half, dtype=torch.float64, device=DEV) / dh)
+    ang = torch.arange(n_tok, dtype=torch.float64, device=DEV)[:, None, None] * inv
+
+    def rope(t):
+        t = t.reshape(n_tok, -1, dh)
+        a, b = t[..., :half], t[..., half:]
+        return torch.cat([a * ang.cos() - b * ang.sin(), a * ang.sin() + b * ang.cos()],
+                         -1).reshape(n_tok, -1)
+
+    xd = x.double()
+    ref = dict(q=rope(y[:, :nq]), k=rope(y[:, nq:nq + nkv]), v=y[:, nq + nkv:],
+               xt=xd + out["q"].double() @ wo.double().t(), x_out=xd.clone())
+    n2 = xd * torch.rsqrt(xd.square().mean(1, keepdim=True) + 1e-6) * g2.double()
+    for e in range(1, E + 1):
+        rows, slot = (eidx == e).nonzero(as_tuple=True)
+        u = n2[rows]
+        h = torch.nn.functional.silu(u @ wg[e - 1].double().t()) * (u @ wu[e - 1].double().t())
+        ref["x_out"].index_add_(0, rows, (h @ wd[e - 1].double().t())
+                                * gate[rows, slot].double()[:, None])
+    for n, t in out.items():
+        assert_close(npy(t), npy(ref[n]), "f32", n)
+
+
+@pytest.mark.parametrize("H,Hkv,dh,G,w,lens", [
+    (2, 1, 64, 64, 50, [1, 63, 64, 65, 700]), (4, 2, 64, 32, 1000, [300, 31]),
+    (3, 1, 128, 32, 40, [500, 33, 1]), (2, 2, 128, 64, 200, [161]),
+])
+def test_f32_attention(H, Hkv, dh, G, w, lens):
+    """fp32 attention, decode and prefill of the last 5 tokens, over every
+    width; slots past a pool's length hold infinities."""
+    B, act, T = len(lens), "f32", 5
+    c = tr.make_cfg(256, H, Hkv, dh, w, 4, 1, 512, G, act)
+    cache = tr.KVCache(c, B, max(lens) + T)
+    rng = gen.stream(62, "f32attn", dh, G)
+    kv = {}
+    for b, n in enumerate(lens):
+        n += T
+        k, v = gen.kv_block(62 + b, n, Hkv, dh, act, 0.8)
+        bits = rng.integers(0, 4, n).astype(np.uint8)
+        kv[b] = (k, v, bits)
+        bad = np.full((40, Hkv, dh), np.inf, np.float32)     # left behind by an earlier sequence
+        if n > 40:
+            _append(c, cache, b, bad, bad, np.full(40, 3, np.uint8), act)
+            cache.reset_seq(b)
+        _append(c, cache, b, k, v, bits, act)
+    assert cache.status() == 0
+    q = gen.normal(62, "f32_q", (B, T, H, dh), 0.8)
+    modes = rng.choice(3, size=(B, T, H), p=[0.1, 0.45, 0.45]).astype(np.uint8)
+    modes[:, -1, 0] = 2
+    modes[:, -1, -1] = 1
+    od, op = torch.empty(B, H * dh, device=DEV), torch.empty(B * T, H * dh, device=DEV)
+    tr.attn_decode(c, B, to_dev(q[:, -1].reshape(B, -1), torch.float32), cache,
+                   to_dev(modes[:, -1], torch.uint8), od, ws=tr.workspace(c, tr.OP_ATTN_DECODE, B, 1))
+    cmp = tr.CompactionBuffers(c, B, T)
+    cc = oracle.compact(modes.reshape(B * T, H), np.zeros((B * T, 1), np.int32), B, T, H, 4, 1)
+    cmp.attn_cnt.copy_(torch.from_numpy(cc["attn_cnt"]))
+    cmp.attn_idx.copy_(torch.from_numpy(np.maximum(cc["attn_idx"], 0).reshape(-1)))
+    tr.attn_prefill(c, B, T, to_dev(q.reshape(B * T, -1), torch.float32), cache,
+                    to_dev(modes.reshape(B * T, H), torch.uint8), cmp.struct, op)
+    torch.cuda.synchronize()
+    for b, n in enumerate(lens):
+        khat, vhat, _ = oracle.layer.store_kv(*kv[b], dict(G=G))
+        ref = oracle.attention_seq(q[b].astype(np.float64), np.arange(n, n + T), khat, vhat,
+                                   modes[b], w)
+        assert_close(npy(op).reshape(B, T, H, dh)[b], ref, act, f"prefill o[b={b}]")
+        assert_close(npy(od).reshape(B, H, dh)[b], ref[-1], act, f"decode o[b={b}]")
