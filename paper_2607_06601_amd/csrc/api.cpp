@@ -206,33 +206,30 @@ RelaxWs carve_relax(Carve &cv, const triroute_cfg &c, int N) {
 
 // The relaxed backward's scratch beyond the forward's: taps of the
 // recomputed trunk, the recomputed tail's decisions (discarded), the
-// per-token gradients, [n1; psi] and its gradient, and the gram partials.
+// per-token gradients and the partial sums.
 struct RelaxBwdWs {
-  float *a1, *hpre, *dz, *dh, *da1, *u, *tgr, *lmsq, *s, *ds, *part, *G, *dc;
+  float *a1, *hpre, *dz, *dh, *da1, *u, *tgr, *lmsq, *cx, *part, *G, *dc;
   double *lmsq_sum;
-  void *n1;
   uint8_t *mode, *bit;
   int32_t *eidx;
   float *egate;
 };
 RelaxBwdWs carve_relax_bwd(Carve &cv, const triroute_cfg &c, int N) {
-  const int NZ = 3 * tr::attn_groups(c) + c.n_experts + 5, K1 = c.d_model + c.d_psi;
+  const int NZ = 3 * tr::attn_groups(c) + c.n_experts + 5;
   RelaxBwdWs w;
   w.a1 = cv.take<float>(size_t(N) * 128);
   w.hpre = cv.take<float>(size_t(N) * 128);
-  w.dz = cv.take<float>(size_t(N) * NZ);
+  w.dz = cv.take<float>(size_t(N) * 128);
   w.dh = cv.take<float>(size_t(N) * 128);
   w.da1 = cv.take<float>(size_t(N) * 128);
   w.u = cv.take<float>(size_t(N) * 128);
   w.tgr = cv.take<float>(size_t(N) * 128);
   w.lmsq = cv.take<float>(size_t(N) * 4);
-  w.s = cv.take<float>(size_t(N) * K1);
-  w.ds = cv.take<float>(size_t(N) * K1);
+  w.cx = cv.take<float>(N);
   w.part = cv.take<float>(tr::relax_grad_part_floats(c, N));
   w.G = cv.take<float>(size_t(NZ) * 128);
   w.dc = cv.take<float>(NZ);
   w.lmsq_sum = cv.take<double>(4);
-  w.n1 = cv.take<uint8_t>(size_t(N) * c.d_model * act_bytes(c));
   w.mode = cv.take<uint8_t>(size_t(N) * c.n_heads);
   w.bit = cv.take<uint8_t>(N);
   w.eidx = cv.take<int32_t>(size_t(N) * c.top_k);
@@ -830,7 +827,8 @@ int triroute_router_relaxed_backward(const triroute_cfg *cfg, int B, int T, cons
   tap.z = xw.z;
   tap.a1 = bw.a1;
   tap.hpre = bw.hpre;
-  CHECK_HIP(tr::launch_router(*cfg, N, x, psi, wf, bw.n1, bw.mode, bw.bit, bw.eidx, bw.egate,
+  // (its n1 is not wanted)
+  CHECK_HIP(tr::launch_router(*cfg, N, x, psi, wf, nullptr, bw.mode, bw.bit, bw.eidx, bw.egate,
                               rw.rinv, rw.u, nullptr, st, tap),
             "router launch");
   tr::RelaxBwdJob j;
@@ -842,7 +840,7 @@ int triroute_router_relaxed_backward(const triroute_cfg *cfg, int B, int T, cons
   j.tau_a = p->tau_a; j.tau_b = p->tau_b; j.zeta = p->zeta; j.alpha = p->alpha; j.beta = p->beta;
   j.gamma = p->gamma;
   j.dz = bw.dz; j.dh = bw.dh; j.da1 = bw.da1; j.u = bw.u; j.tgr = bw.tgr; j.lmsq = bw.lmsq;
-  j.s = bw.s; j.ds = bw.ds; j.part = bw.part; j.G = bw.G; j.dc = bw.dc; j.lmsq_sum = bw.lmsq_sum;
+  j.rinv = rw.rinv; j.cx = bw.cx; j.part = bw.part; j.G = bw.G; j.dc = bw.dc; j.lmsq_sum = bw.lmsq_sum;
   j.out = tr::RelaxGradOut{go->dW1, go->db1, go->dW2, go->db2, go->dgr, go->dWa, go->dca,
                            go->dWe, go->dce, go->dWb, go->dcb, go->dg1, go->dx, go->dpsi,
                            go->lm_norm};

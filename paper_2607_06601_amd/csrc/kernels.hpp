@@ -170,7 +170,8 @@ struct RelaxBwdJob {
   float rho_m;
   float tau_a, tau_b, zeta, alpha, beta, gamma;
   // scratch
-  float *dz, *dh, *da1, *u, *tgr, *lmsq, *s, *ds, *part, *G, *dc;
+  const float *rinv;  // the first norm's row scales (the recomputed router's)
+  float *dz, *dh, *da1, *u, *tgr, *lmsq, *cx, *part, *G, *dc;
   double *lmsq_sum;
   RelaxGradOut out;
 };

@@ -351,3 +351,81 @@ def test_f32_attention(H, Hkv, dh, G, w, lens):
                                    modes[b], w)
         assert_close(npy(op).reshape(B, T, H, dh)[b], ref, act, f"prefill o[b={b}]")
         assert_close(npy(od).reshape(B, H, dh)[b], ref[-1], act, f"decode o[b={b}]")
+
+
+# --------------------------------------------------- controller's backward
+@pytest.mark.parametrize("B,T,d,dpsi,H,E,k,groups,act", [
+    (1, 1, 64, 0, 2, 1, 1, 0, "bf16"),          # one token, one column tile, no side features
+    (1, 31, 128, 4, 4, 3, 2, 2, "f32"),         # fewer tokens than a tile
+    (2, 67, 192, 32, 4, 2, 3, 1, "bf16"),       # a ragged wave of tokens, the most side features
+    (1, 129, 2048, 8, 16, 16, 2, 0, "bf16"),    # one token past a block, many column tiles
+    (3, 683, 64, 8, 30, 12, 2, 0, "f32"),       # 107 logits; several chunks, few column tiles
+])
+def test_relaxed_backward_tiles(B, T, d, dpsi, H, E, k, groups, act):
+    """Gradients of the relaxed controller against fp64 torch autograd at the
+    edges of the token, column and chunk tiles, within the fp32 bound (the
+    sums run over at most 2049 tokens)."""
+    A, N, dev = groups or H, B * T, dict(device=DEV)
+    c = tr.make_cfg(d, H, 2, 64, 64, E, k, 128, 64, act, d_psi=dpsi, attn_groups=groups)
+    g = torch.Generator(**dev)
+    g.manual_seed(71)
+
+    def rnd(*shape, std=1.0):
+        return torch.randn(shape, generator=g, **dev) * std
+
+    w = dict(g1=1 + rnd(d, std=0.02), W1=rnd(128, d + dpsi, std=0.05), b1=rnd(128, std=0.02),
+             W2=rnd(128, 128, std=0.1), b2=rnd(128, std=0.02), gr=1 + rnd(128, std=0.02),
+             Wa=rnd(3 * A, 128, std=0.1), ca=rnd(3 * A, std=0.1), We=rnd(E + 1, 128, std=0.1),
+             ce=rnd(E + 1, std=0.1), Wb=rnd(4, 128, std=0.1), cb=rnd(4, std=0.1))
+    rw = tr.RouterW(*(t.data_ptr() for t in w.values()))
+    x, psi = rnd(N, d).to(torch_act(act)), rnd(N, max(dpsi, 1))[:, :dpsi].contiguous()
+    pos = torch.arange(N, dtype=torch.int32, **dev)
+    ga, gb = rnd(N, A, 3), rnd(N, 4)
+    p = tr.RelaxParams(g_attn=ga.data_ptr(), g_bits=gb.data_ptr(), pos=pos.data_ptr(), tau_a=1.3,
+                       tau_b=0.8, zeta=0.99, alpha=0.01, beta=0.001, gamma=0.1)
+    f64, dec = dict(dtype=torch.float64, **dev), {}
+    o = dict(y_attn=torch.empty(N, A, 3, **dev), y_bits=torch.empty(N, 4, **dev),
+             c_flops=torch.empty(N, **dev), c_mem=torch.empty(N, **dev),
+             stats=torch.empty(tr.RELAX_NSTAT, **f64), usage_exp=torch.empty(2, E + 1, **f64))
+    fwd = tr.RelaxOut(**{n: t.data_ptr() for n, t in o.items()})
+    eidx, egate = torch.empty(N, k, dtype=torch.int32, **dev), torch.empty(N, k, **dev)
+    cmp = tr.CompactionBuffers(c, B, T)
+    tr.router_relaxed(c, B, T, x, psi, rw, p, torch.empty_like(x),
+                      torch.empty(N, H, dtype=torch.uint8, **dev),
+                      torch.empty(N, dtype=torch.uint8, **dev), eidx, egate, cmp.struct, fwd,
+                      tr.workspace(c, tr.OP_ROUTER_RELAXED, B, T))
+    up = dict(a=rnd(N, A, 3), b=rnd(N, 4), e=rnd(N, k))
+    rho = torch.tensor([1.5, 0.8, 2.5], **f64)
+    gin = tr.RelaxGradIn(g_attn=up["a"].data_ptr(), g_bits=up["b"].data_ptr(),
+                         g_gate=up["e"].data_ptr(), rho=rho.data_ptr(), rho_m=0.0)
+    out = {"d" + n: torch.full_like(t, float("nan")) for n, t in w.items()}
+    out.update(dx=torch.full((N, d), float("nan"), **dev), dpsi=torch.full((N, dpsi), float("nan"), **dev))
+    ws = tr.workspace(c, tr.OP_ROUTER_RELAXED_BACKWARD, B, T)
+    ws.fill_(0xFF)
+    print(f"relaxed backward N={N} d={d} dpsi={dpsi} A={A}", flush=True)
+    tr.router_relaxed_backward(c, B, T, x, psi, rw, p, fwd, eidx, egate, gin,
+                               tr.RelaxGradOut(**{n: t.data_ptr() for n, t in out.items()}), ws)
+    torch.cuda.synchronize()
+    v = {n: t.double().requires_grad_(True) for n, t in dict(w, x=x, psi=psi).items()}
+    n1 = v["x"] * torch.rsqrt(v["x"].square().mean(1, keepdim=True) + 1e-6) * v["g1"]
+    a1 = torch.cat([n1, v["psi"]], 1) @ v["W1"].t() + v["b1"]
+    h = (0.5 * a1 * (1 + torch.erf(a1 / 2 ** 0.5))) @ v["W2"].t() + v["b2"]
+    hh = h * torch.rsqrt(h.square().mean(1, keepdim=True) + 1e-6) * v["gr"]
+    za, ze, zb = (hh @ v[a].t() + v[b] for a, b in (("Wa", "ca"), ("We", "ce"), ("Wb", "cb")))
+    za = za.view(N, A, 3)
+    pe, sel = torch.softmax(ze, 1), eidx.long()
+    gate = pe.gather(1, sel)
+    gate = gate / gate.sum(1, keepdim=True)
+    ya, yb = torch.softmax((za + ga) / 1.3, -1), torch.softmax((zb + gb) / 0.8, -1)
+    loss = (up["a"] * ya).sum() / rho[0] + (up["e"] * gate).sum() / rho[1] + (up["b"] * yb).sum() / rho[2]
+    st, us = o["stats"], o["usage_exp"]
+    for z, f in ((za.reshape(-1, 3), st[tr.RS_F_ATTN:tr.RS_F_ATTN + 3]), (ze, us[0]),
+                 (zb, st[tr.RS_F_BITS:tr.RS_F_BITS + 4])):
+        P = torch.softmax(z, 1).mean(0)
+        ent = -(P * P.log()).sum()
+        loss = loss + 0.01 * len(f) * (f * P).sum() + 0.001 * torch.logsumexp(z, 1).square().mean() \
+            + 0.1 * (0.99 * np.log(len(f)) - ent).clamp_min(0)
+    loss.backward()
+    for n, t in out.items():
+        if t.numel():
+            assert_close(npy(t), npy(v[n[1:]].grad), "f32", n)
