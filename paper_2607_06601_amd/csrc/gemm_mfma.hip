@@ -679,9 +679,14 @@ __device__ __forceinline__ void store_acc(const P &p, float *C, const f32x4_t (&
     }
 }
 
-template <class P, int BM, int BN, int WM, int WN, int BK, int S>
-__global__ __launch_bounds__(64 * WM * WN, 1) void gemm_mfma_kernel(P p, int K, int ny) {
-  constexpr int NW = WM * WN, NT = 64 * NW;  // waves, threads
+// KW > 1: the block holds KW groups of WM x WN waves, each with its own stages
+// over a KW-th of K; the partial tiles are added in group order at the end.
+// A few rows against a small weight give one block a CU at most, which walks
+// K in a chain of round trips to memory; KW groups make the chain that much
+// shorter.
+template <class P, int BM, int BN, int WM, int WN, int BK, int S, int KW>
+__global__ __launch_bounds__(64 * WM * WN * KW, 1) void gemm_mfma_kernel(P p, int K, int ny) {
+  constexpr int NW = WM * WN, NT = 64 * NW * KW;  // waves of a K group, threads
   constexpr int TM = BM / WM, TN = BN / WN;  // wave tile
   constexpr int MI = TM / 16, NI = TN / 16;  // 16 x 16 MFMA tiles per wave
   constexpr int RB = BK * 2;                 // bytes per operand row per K step
@@ -692,8 +697,10 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_mfma_kernel(P p, int K, 
   static_assert(STAGE % (1024 * NW) == 0 && TN % 64 == 0, "whole transfers, 64-column slices");
   static_assert(S >= 2 && S <= 6 && (BK == 32 || BK == 64), "pipeline shape");
   constexpr int NC = P::out_cols(BN), LDC = NC + 16;  // staged output tile (fp32)
-  constexpr int SMEM = S * STAGE > BM * LDC * 4 ? S * STAGE : BM * LDC * 4;
-  __shared__ __align__(1024) uint8_t smem[SMEM];
+  constexpr int PART = BM * BN * 4;                    // a group's partial tile
+  constexpr int OUT = BM * LDC * 4 > (KW - 1) * PART ? BM * LDC * 4 : (KW - 1) * PART;
+  constexpr int SMEM = KW * S * STAGE > OUT ? KW * S * STAGE : OUT;
+  __shared__ __align__(1024) uint8_t smem_all[SMEM];
   GroupScan gs;
   if constexpr (P::GROUPED) gs = group_scan(BM, p.cnt, p.E);
   const int total = p.tiles(BM, ny, gs);
@@ -701,8 +708,11 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_mfma_kernel(P p, int K, 
   const int t = xcd_tile(blockIdx.x, total);
   MTile tc;
   if (!p.map(t / ny, t % ny, BM, BN, tc, gs)) return;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int kg = KW > 1 ? (tid >> 6) / NW : 0, wave = KW > 1 ? (tid >> 6) % NW : tid >> 6;
   const int wm = wave / WN, wn = wave % WN;
+  uint8_t *smem = smem_all + kg * S * STAGE;  // the group's stages
+  const int nk = K / BK / KW;                 // its K steps, from step kg nk on
   // Transfer j of this wave fills stage rows RPT g .. RPT g + RPT - 1
   // (g = wave IPW + j; A rows first, then B rows).  Lane l writes LDS chunk
   // l % CPR of row RPT g + l / CPR, which holds the source chunk that swz
@@ -722,7 +732,7 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_mfma_kernel(P p, int K, 
       row = p.b_row(tc, rr - BM);
       if (!row) row = b_fallback;
     }
-    src[j] = (const uint8_t *)row + c * 16;
+    src[j] = (const uint8_t *)row + c * 16 + kg * nk * RB;
   }
   const uint32_t sbase = lds_addr(smem) + wave * IPW * 1024;
   auto issue = [&](int kt, int stage) {
@@ -734,7 +744,6 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_mfma_kernel(P p, int K, 
   for (int i = 0; i < MI; ++i)
 #pragma unroll
     for (int j = 0; j < NI; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  const int nk = K / BK;
 #pragma unroll
   for (int s0 = 0; s0 < S - 1; ++s0)
     if (s0 < nk) issue(s0, s0);
@@ -765,8 +774,34 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_mfma_kernel(P p, int K, 
     }
   }
   __syncthreads();  // every wave is done with the operand stages
-  float *C = (float *)smem;
-  store_acc<P, MI, NI, TM, TN, LDC>(p, C, acc, wm, wn, lane);
+  float *C = (float *)smem_all;
+  if constexpr (KW > 1) {
+    // partial tiles of groups 1 .. KW - 1, [group][wave][register][lane]
+    float *part = C + wave * (PART / 4 / NW) + lane;
+    if (kg > 0) {
+      float *o = part + (kg - 1) * (PART / 4);
+#pragma unroll
+      for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) o[((mi * NI + ni) * 4 + i) * 64] = acc[mi][ni][i];
+    }
+    __syncthreads();
+    if (kg == 0) {
+#pragma unroll
+      for (int g = 0; g < KW - 1; ++g)
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+          for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              acc[mi][ni][i] += part[g * (PART / 4) + ((mi * NI + ni) * 4 + i) * 64];
+    }
+    __syncthreads();
+  }
+  if (KW == 1 || kg == 0) store_acc<P, MI, NI, TM, TN, LDC>(p, C, acc, wm, wn, lane);
   __syncthreads();
   p.template epilogue<BM, NC, LDC, NT>(tc, C, tid);
 }
@@ -1021,11 +1056,11 @@ __global__ __launch_bounds__(256, 1) void gemm_w4_kernel(P p, int K, int ny) {
 // ------------------------------------------------------------------ launchers
 // m_tiles bounds the row tiles (for grouped problems: the most any routing
 // can need); the kernel takes the actual count from the problem.
-template <class P, int BM, int BN, int WM, int WN, int BK, int S>
+template <class P, int BM, int BN, int WM, int WN, int BK, int S, int KW = 1>
 static hipError_t launch(const P &p, int K, int m_tiles, int n_tiles, hipStream_t st) {
   if (m_tiles > 0 && n_tiles > 0)
-    gemm_mfma_kernel<P, BM, BN, WM, WN, BK, S>
-        <<<m_tiles * n_tiles, 64 * WM * WN, 0, st>>>(p, K, n_tiles);
+    gemm_mfma_kernel<P, BM, BN, WM, WN, BK, S, KW>
+        <<<m_tiles * n_tiles, 64 * WM * WN * KW, 0, st>>>(p, K, n_tiles);
   return hipGetLastError();
 }
 
@@ -1104,6 +1139,11 @@ static bool w4_rounds(int N, int c128, float t) {
 // against 13.9 us; 1.3B QKV 512 tokens, 192 tiles: 29.5 against 23.5 us).
 static bool few_tiles(int N, int c128) { return tiles64(N, c128) < 192; }
 
+// At most one 32 x 64 block a CU: two K groups in the block (1.3B O-projection,
+// 1 to 128 tokens, 32 to 128 blocks: 12.4 to 13.0 -> 8.7 to 10.1 us; at 352
+// blocks 15.0 -> 19.4 us).
+static bool split_k(int blocks, int K) { return blocks <= cu_count() && K % 128 == 0; }
+
 // Up to 288 tiles of 64 rows, three stages: the blocks wait on each step's
 // transfers (1.3B O-projection, 1000 tokens, 256 tiles: 19.2 us, with two
 // stages 29.3, the 128-row tiles 22.2).
@@ -1138,7 +1178,10 @@ hipError_t mfma_qkv(const triroute_cfg &cfg, int B, int Tq, const void *n1,
   p.Ncols = (cfg.n_heads + 2 * cfg.n_kv_heads) * cfg.head_dim;
   const int c128 = (p.Ncols + 127) / 128;
   // Few tokens (decode): the product streams the weights; 32-row tiles one
-  // head wide put one block on every head and row tile.
+  // head wide put one block on every head and row tile.  (Two K groups a
+  // block would take 1.5 us off 9.3 on the 410M layer, but keys and values go
+  // into the cache, and every other tile here sums them in one order of K: a
+  // token's stored codes do not depend on how many tokens came with it.)
   if (few_tiles(p.N, c128)) {
     if (p.dh == 64)
       return launch<QkvM, 32, 64, 2, 1, 64, 4>(p, cfg.d_model, (p.N + 31) / 32, (p.Ncols + 63) / 64, st);
@@ -1179,6 +1222,8 @@ hipError_t mfma_oproj(const triroute_cfg &cfg, int N, const void *x, const void 
   p.d = cfg.d_model;
   p.K = cfg.n_heads * cfg.head_dim;
   const int c128 = (p.d + 127) / 128;
+  if (few_tiles(N, c128) && split_k((N + 31) / 32 * ((p.d + 63) / 64), p.K))
+    return launch<OprojM, 32, 64, 2, 1, 64, 4, 2>(p, p.K, (N + 31) / 32, (p.d + 63) / 64, st);
   if (few_tiles(N, c128))  // few tokens: weight streaming, narrow tiles as for QKV
     return launch<OprojM, 32, 64, 2, 1, 64, 4>(p, p.K, (N + 31) / 32, (p.d + 63) / 64, st);
   const bf16 *lo;
@@ -1231,7 +1276,12 @@ hipError_t mfma_moe(const triroute_cfg &cfg, int N, const void *n2, const trirou
                   span32({{p1.n2, size_t(Nk) * d * sizeof(bf16)}}, &alo);
   const int ny = (dff + 127) / 128;
   hipError_t err;
-  if (r <= 24)
+  if (r <= 24 && d >= 2048 && d % 128 == 0)
+    // a long K: two K groups of three stages have more of the weights in
+    // flight (1.3B, 32 to 100 tokens: the block 204 to 213 -> 193 to 202 us;
+    // 410M, K 1024: 40 -> 43)
+    err = launch<Moe1M, 32, 64, 2, 1, 64, 3, 2>(p1, d, Nk / 32 + E, (dff + 31) / 32, st);
+  else if (r <= 24)
     err = launch<Moe1M, 32, 64, 2, 1, 64, 4>(p1, d, Nk / 32 + E, (dff + 31) / 32, st);
   else if (r <= 64)
     err = launch<Moe1M, 64, 128, 2, 2, 64, 3>(p1, d, Nk / 64 + E, (dff + 63) / 64, st);
@@ -1263,6 +1313,10 @@ hipError_t mfma_moe(const triroute_cfg &cfg, int N, const void *n2, const trirou
     if (r > 64 && row_tiles(128) * cols >= 256)
       return launch<Moe2M, 128, 128, 4, 2, 64, 3>(p2, K, Nk / 128 + E, cols, st);
     if (r > 64) return launch<Moe2M, 64, 128, 2, 2, 64, 3>(p2, K, Nk / 64 + E, cols, st);
+    // (with fewer assignments than experts not every expert has a tile: 32 x 64
+    // tiles, two K groups a block; 1.3B, 1 token: the block 50 -> 35 us, 4 108 -> 96)
+    if (Nk <= E && K % 128 == 0 && (K >= 2048 || Nk * 2 * cols <= 128))
+      return launch<Moe2M, 32, 64, 2, 1, 64, 4, 2>(p2, K, Nk / 32 + E, (d + 63) / 64 * p2.ksplit, st);
     if (row_tiles(64) * cols >= 256)
       return launch<Moe2M, 64, 128, 2, 2, 64, 2>(p2, K, Nk / 64 + E, cols, st);
     return launch<Moe2M, 32, 64, 2, 1, 64, 4>(p2, K, Nk / 32 + E, (d + 63) / 64 * p2.ksplit, st);

@@ -130,6 +130,8 @@ def test_prefill_split_key_ranges(monkeypatch, B, T, H, Hkv, dh, w, ctx, pages):
 
 # ------------------------------------------------------- GEMM tile choices
 @pytest.mark.parametrize("H,Hkv,dh,d,n_tok", [
+    (4, 1, 64, 128, 1), (3, 1, 64, 128, 33),           # O-projection: two K groups (K 192: one)
+    (12, 2, 64, 1024, 512), (12, 2, 64, 1024, 513),    # 256 blocks of them and more
     (4, 1, 64, 256, 4032), (4, 1, 64, 256, 4033),      # 32-row tiles to 64 x 128 (3 columns of 128)
     (3, 1, 64, 192, 6200),                             # 320 columns: the last tile half empty
     (16, 4, 128, 128, 768), (16, 4, 128, 128, 769),    # 288 tiles of 64 rows; 128 x 128, one round
@@ -178,6 +180,8 @@ def test_projection_tiles(H, Hkv, dh, d, n_tok):
 
 
 @pytest.mark.parametrize("E,k,d,dff,n_tok,skew", [
+    (4, 1, 256, 512, 1, 0), (8, 2, 2048, 4096, 4, 0),     # fewer assignments than experts: K groups
+    (8, 2, 2048, 384, 60, 0), (8, 2, 2048, 384, 100, 1),  # long K: K groups in gate/up
     (4, 1, 256, 512, 124, 0), (4, 1, 256, 512, 125, 0),   # 24 rows an expert and one more
     (4, 1, 256, 512, 324, 0), (4, 1, 256, 512, 325, 0),   # 64 and 65
     (16, 2, 1024, 256, 300, 0),                           # down: 64 x 128 over K halves
