@@ -439,10 +439,11 @@ int check_paged_args(int n_seq, int capacity, int PT, const int32_t *np) {
 hipError_t run_attn_prefill(const triroute_cfg &c, const triroute_kv_cache &kc, int B, int T,
                             const int32_t *seq_ids, const void *q, const uint8_t *mode,
                             const triroute_compaction &cmp, void *o, float *part,
-                            size_t part_bytes, hipStream_t st) {
-  // the rows no attention block writes: skipped heads, dropped rows
-  hipError_t e = tr::launch_attn_zero_rows(c, B, T, mode, seq_ids, kc.n_seq, o, st);
-  if (e != hipSuccess) return e;
+                            size_t part_bytes, bool zeroed, hipStream_t st) {
+  if (!zeroed) {  // the rows no attention block writes: skipped heads, dropped rows
+    const hipError_t e = tr::launch_attn_zero_rows(c, B, T, mode, seq_ids, kc.n_seq, o, st);
+    if (e != hipSuccess) return e;
+  }
   const tr::CacheView v = tr::make_view(c, kc);
   return c.act == TRIROUTE_BF16 ? tr::launch_attn_mfma_prefill(c, v, B, T, seq_ids, q, mode, cmp, o, part,
                                                                  part_bytes, st)
@@ -879,7 +880,7 @@ int triroute_attn_prefill(const triroute_cfg *cfg, int B, int T, const int32_t *
   TRY(check_ws(*cfg, TRIROUTE_OP_ATTN_PREFILL, B, T, ws, ws_bytes));
   // (the call takes no workspace, so its key ranges are never split)
   CHECK_HIP(run_attn_prefill(*cfg, *cache, B, T, seq_ids, q, mode, *cmp, o, nullptr, 0,
-                             (hipStream_t)stream),
+                             false, (hipStream_t)stream),
             "attn_prefill launch");
   return TRIROUTE_OK;
 }
@@ -983,19 +984,29 @@ static int layer_impl(const triroute_cfg *cfg, int B, int T, bool decode, const 
     CHECK_HIP(tr::launch_router(*cfg, N, x, psi, *rw, L.n1, L.mode, L.bit, L.eidx, L.egate, r.rinv,
                                 r.u, &job, st),
               "router launch");
-    // decode attention reads the modes themselves: no attention lists
-    CHECK_HIP(tr::launch_compact(*cfg, B, T, L.mode, L.eidx, L.cmp, r.hist, st, !decode),
-              "compaction");
+    // The lists, and beside them what else only waits for the decisions: the
+    // append's slots (several tokens a row; they move the sequence lengths,
+    // which the rotation table has read) and the attention's zero rows.  The
+    // append's scratch takes the place of the trunk's, which is used up; the
+    // histograms behind it stay for the lists' second half, which runs beside
+    // the append.  Decode attention reads the modes themselves: no attention
+    // lists, and one chunk of assignments needs no histograms.
+    Carve kc(ws);
+    kc.used = scratch_at;
+    const tr::KvWs kw = carve_kv(kc, *cfg, B, T);
+    const tr::AppendJob app{tr::make_view(*cfg, *cache), seq_ids, L.bit, kw, T > 1};
+    const tr::ScatterJob lists = tr::make_scatter_job(*cfg, N, L.eidx, L.cmp, r.hist);
+    const bool one = T == 1 && lists.nbe == 1;
+    if (!decode || !one)
+      CHECK_HIP(tr::launch_lists(*cfg, B, T, L.mode, L.eidx, L.cmp, r.hist, !decode, &app,
+                                 decode ? nullptr : L.o, st),
+                "list launch");
+    if (T == 1 && !one) CHECK_HIP(tr::launch_scatter(lists, st), "list launch");
     CHECK_HIP(tr::launch_qkv(*cfg, B, T, L.n1, *dw, seq_len, seq_ids, cache->n_seq, L.q, L.k, L.v,
                              rope, true, st),
               "qkv launch");
-  }
-  {
-    Carve sc(ws);
-    sc.used = scratch_at;
-    const tr::KvWs kw = carve_kv(sc, *cfg, B, T);
-    CHECK_HIP(tr::launch_kv_append(*cfg, tr::make_view(*cfg, *cache), B, T, seq_ids, L.k, L.v, L.bit,
-                                   kw, st),
+    CHECK_HIP(tr::launch_kv_append(*cfg, app.cv, B, T, seq_ids, L.k, L.v, L.bit, kw, st, T > 1,
+                                   T > 1 || one ? &lists : nullptr),
               "kv_append launch");
   }
   if (decode) {
@@ -1008,7 +1019,7 @@ static int layer_impl(const triroute_cfg *cfg, int B, int T, bool decode, const 
     // the scratch the expert block uses later holds the attention's partials
     CHECK_HIP(run_attn_prefill(*cfg, *cache, B, T, seq_ids, L.q, L.mode, L.cmp, L.o,
                                (float *)((uint8_t *)ws + scratch_at),
-                               op_bytes(*cfg, TRIROUTE_OP_MOE, B, T), st),
+                               op_bytes(*cfg, TRIROUTE_OP_MOE, B, T), true, st),
               "attn_prefill launch");
   }
   CHECK_HIP(tr::launch_oproj(*cfg, N, x, L.o, *dw, L.xt, st), "oproj launch");

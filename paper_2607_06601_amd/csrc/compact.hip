@@ -3,178 +3,168 @@
 //
 //   attention: per (b, h), the ascending t of local and of full queries
 //   experts  : per expert 1..E, the ascending assignment ids a = i*k + slot
-#include "kernels.hpp"
+#include "lists.hpp"
 
 namespace tr {
 
-constexpr int CHUNK = 1024;  // assignments per expert block
-
-// Blocks [0, B*H): attention lists of one (b, h).  Blocks [B*H, +nbe):
-// per-block expert histograms.
-__global__ __launch_bounds__(256) void compact_count_kernel(
-    const uint8_t *__restrict__ mode, const int32_t *__restrict__ eidx, int B, int T, int H,
-    int E1, int Nk, int32_t *__restrict__ attn_cnt, int32_t *__restrict__ attn_idx,
-    int32_t *__restrict__ hist) {
-  __shared__ int wcnt[2][4];
+// Blocks [0, nattn): attention lists of one (b, h), 1024 tokens a round; then
+// nbe blocks: expert histograms of a chunk of assignments; then nslot blocks:
+// a batch row's slots (kv_slots_rows); the rest: the attention output rows that
+// no attention block writes, zeroed (skipped heads, i.e. any mode but local or
+// full, and every head of a row whose sequence id lies outside the cache), a
+// thread per (token, head) row.  All read the decisions alone.  (As launches
+// of their own: 1.3B, 16384 tokens, lists 16 us in 256-token rounds, slots
+// 12, zeroing 8; 410M, 333 tokens, 4.4 + 4 + 3.2.)
+struct ListsArgs {
+  const uint8_t *mode;
+  const int32_t *eidx;
+  int B, T, H, E1, Nk, nattn, nbe, nslot;
+  int32_t *attn_cnt, *attn_idx, *hist;
+  CacheView cv;
+  const int32_t *seq_ids;
+  const uint8_t *bit;
+  int32_t *old_len;
+  uint4 *o;  // rows of `chunks` 16-byte pieces
+  int chunks;
+  uint32_t pairs;
+};
+__global__ __launch_bounds__(1024) void lists_kernel(ListsArgs a) {
+  __shared__ int wcnt[2][16];
   __shared__ int lh[64];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int bid = blockIdx.x;
-  if (bid < B * H) {
+  int bid = blockIdx.x;
+  const int T = a.T, H = a.H;
+  if (bid < a.nattn) {
     const int b = bid / H, h = bid % H;
     int base[2] = {0, 0};
-    for (int t0 = 0; t0 < T; t0 += 256) {
+    for (int t0 = 0; t0 < T; t0 += 1024) {
       const int t = t0 + tid;
-      const int m = t < T ? mode[(int64_t(b) * T + t) * H + h] : 0;
+      const int m = t < T ? a.mode[(int64_t(b) * T + t) * H + h] : 0;
       uint64_t bal[2];
       bal[0] = __ballot(m == 1);
       bal[1] = __ballot(m == 2);
-      if (lane == 0) {
-        wcnt[0][w] = __popcll(bal[0]);
-        wcnt[1][w] = __popcll(bal[1]);
-      }
+      if (lane < 2) wcnt[lane][w] = __popcll(bal[lane]);
       __syncthreads();
+      int before[2] = {0, 0}, all[2] = {0, 0};
+#pragma unroll
+      for (int ww = 0; ww < 16; ++ww)
+#pragma unroll
+        for (int mm = 0; mm < 2; ++mm) {
+          const int n = wcnt[mm][ww];
+          before[mm] += ww < w ? n : 0;
+          all[mm] += n;
+        }
 #pragma unroll
       for (int mm = 0; mm < 2; ++mm) {
-        if (m == mm + 1) {
-          int off = base[mm] + __popcll(bal[mm] & lanemask_lt());
-          for (int ww = 0; ww < w; ++ww) off += wcnt[mm][ww];
-          attn_idx[(int64_t(bid) * 2 + mm) * T + off] = t;
-        }
+        if (m == mm + 1)
+          a.attn_idx[(int64_t(bid) * 2 + mm) * T + base[mm] + before[mm] +
+                     __popcll(bal[mm] & lanemask_lt())] = t;
+        base[mm] += all[mm];
       }
-#pragma unroll
-      for (int mm = 0; mm < 2; ++mm)
-        base[mm] += wcnt[mm][0] + wcnt[mm][1] + wcnt[mm][2] + wcnt[mm][3];
       __syncthreads();
     }
-    if (tid < 2) attn_cnt[bid * 2 + tid] = base[tid];
+    if (tid < 2) a.attn_cnt[bid * 2 + tid] = tid ? base[1] : base[0];
     return;
   }
-  const int j = bid - B * H;
-  for (int e = tid; e < E1; e += 256) lh[e] = 0;
-  __syncthreads();
-  for (int a = j * CHUNK + tid; a < min(Nk, (j + 1) * CHUNK); a += 256) atomicAdd(&lh[eidx[a]], 1);
-  __syncthreads();
-  for (int e = tid; e < E1; e += 256) hist[j * E1 + e] = lh[e];
-}
-
-// Stable scatter of assignment ids into per-expert lists.  Block j first
-// forms each expert's first output position for its chunk from the chunk
-// histograms (all chunks' totals give the expert offsets; block 0 also
-// writes the counts and offsets).
-__global__ __launch_bounds__(256) void compact_scatter_kernel(const int32_t *__restrict__ eidx,
-                                                              const int32_t *__restrict__ hist,
-                                                              int nbe, int E1, int Nk,
-                                                              int32_t *__restrict__ rows,
-                                                              int32_t *__restrict__ exp_cnt,
-                                                              int32_t *__restrict__ exp_off) {
-  __shared__ int wc[4][64];
-  __shared__ int run[64], tot[64];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int j = blockIdx.x;
-  if (tid < E1) {
-    int before = 0, all = 0;
-    for (int jj = 0; jj < nbe; ++jj) {
-      const int v = hist[jj * E1 + tid];
-      if (jj < j) before += v;
-      all += v;
-    }
-    run[tid] = before;
-    tot[tid] = all;
+  bid -= a.nattn;
+  if (bid < a.nbe) {
+    static_assert(CHUNK == 1024, "one assignment a thread");
+    if (tid < a.E1) lh[tid] = 0;  // E1 <= 64
+    __syncthreads();
+    const int i = bid * CHUNK + tid;
+    if (i < a.Nk) atomicAdd(&lh[a.eidx[i]], 1);
+    __syncthreads();
+    if (tid < a.E1) a.hist[bid * a.E1 + tid] = lh[tid];
+    return;
   }
-  __syncthreads();
-  if (tid < E1) {
-    int start = 0;  // lists of experts 1 .. tid - 1 come first
-    for (int ee = 1; ee < tid; ++ee) start += tot[ee];
-    if (tid >= 1) run[tid] += start;
-    if (j == 0) {
-      exp_cnt[tid] = tot[tid];
-      exp_off[tid] = tid == 0 ? 0 : start + tot[tid];
-    }
+  bid -= a.nbe;
+  if (bid < a.nslot) {
+    kv_slots_rows(a.cv, T, a.seq_ids, a.bit, a.old_len, bid);
+    return;
   }
-  __syncthreads();
-  // (sub rounds past the last assignment are skipped: the bound is uniform
-  // over the block, so every barrier below is still reached by all threads)
-  for (int sub = 0; sub < CHUNK && j * CHUNK + sub < Nk; sub += 256) {
-    const int a = j * CHUNK + sub + tid;
-    const int e = a < Nk ? eidx[a] : -1;
-    int rank = 0;
-    for (int ee = 1; ee < E1; ++ee) {
-      uint64_t bal = __ballot(e == ee);
-      if (e == ee) rank = __popcll(bal & lanemask_lt());
-      if (lane == 0) wc[w][ee] = __popcll(bal);
-    }
-    __syncthreads();
-    if (e >= 1) {
-      int pos = run[e] + rank;
-      for (int ww = 0; ww < w; ++ww) pos += wc[ww][e];
-      rows[pos] = a;
-    }
-    __syncthreads();
-    for (int ee = tid; ee < E1; ee += 256)
-      if (ee >= 1) run[ee] += wc[0][ee] + wc[1][ee] + wc[2][ee] + wc[3][ee];
-    __syncthreads();
+  bid -= a.nslot;
+  const uint32_t pair = uint32_t(bid) * 1024u + uint32_t(tid);  // token * H + head
+  if (pair >= a.pairs) return;
+  const int b = int(pair / (uint32_t(H) * uint32_t(T)));
+  const int s = a.seq_ids ? a.seq_ids[b] : b;
+  const int m = a.mode[pair];
+  if ((m != TRIROUTE_LOCAL && m != TRIROUTE_FULL) || s < 0 || s >= a.cv.n_seq) {
+    uint4 *row = a.o + size_t(pair) * a.chunks;
+    for (int c = 0; c < a.chunks; ++c) row[c] = make_uint4(0u, 0u, 0u, 0u);
   }
 }
 
-// Few assignments (one chunk) and no attention lists (decode): the expert
-// lists by one block in one launch, histogram, offsets and the same stable
-// scatter as the two kernels above (so the same lists).
-__global__ __launch_bounds__(256) void compact_experts_one_kernel(const int32_t *__restrict__ eidx,
-                                                                  int E1, int Nk,
-                                                                  int32_t *__restrict__ rows,
-                                                                  int32_t *__restrict__ exp_cnt,
-                                                                  int32_t *__restrict__ exp_off) {
-  __shared__ int lh[64], run[64];
-  __shared__ int wc[4][64];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  if (tid < E1) lh[tid] = 0;  // E1 <= 64
-  __syncthreads();
-  for (int a = tid; a < Nk; a += 256) atomicAdd(&lh[eidx[a]], 1);
-  __syncthreads();
-  if (tid < E1) {
-    int start = 0;  // lists of experts 1 .. tid - 1 come first
-    for (int ee = 1; ee < tid; ++ee) start += lh[ee];
-    run[tid] = start;
-    exp_cnt[tid] = lh[tid];
-    exp_off[tid] = tid == 0 ? 0 : start + lh[tid];
-  }
-  __syncthreads();
-  for (int sub = 0; sub < Nk; sub += 256) {  // block-uniform bound: every barrier is reached
-    const int a = sub + tid;
-    const int e = a < Nk ? eidx[a] : -1;
-    int rank = 0;
-    for (int ee = 1; ee < E1; ++ee) {
-      const uint64_t bal = __ballot(e == ee);
-      if (e == ee) rank = __popcll(bal & lanemask_lt());
-      if (lane == 0) wc[w][ee] = __popcll(bal);
-    }
-    __syncthreads();
-    if (e >= 1) {
-      int pos = run[e] + rank;
-      for (int ww = 0; ww < w; ++ww) pos += wc[ww][e];
-      rows[pos] = a;
-    }
-    __syncthreads();
-    if (tid >= 1 && tid < E1) run[tid] += wc[0][tid] + wc[1][tid] + wc[2][tid] + wc[3][tid];
-    __syncthreads();
-  }
+__global__ __launch_bounds__(256) void compact_scatter_kernel(ScatterJob J) {
+  scatter_chunk(J, blockIdx.x);
 }
+
 int compact_hist_ints(int N, int k, int E1) { return ((N * k + CHUNK - 1) / CHUNK) * E1; }
+
+ScatterJob make_scatter_job(const triroute_cfg &cfg, int N, const int32_t *eidx,
+                            const triroute_compaction &c, const int32_t *hist) {
+  ScatterJob j;
+  j.eidx = eidx;
+  j.hist = hist;
+  j.E1 = cfg.n_experts + 1;
+  j.Nk = N * cfg.top_k;
+  j.nbe = (j.Nk + CHUNK - 1) / CHUNK;
+  j.rows = c.exp_rows;
+  j.exp_cnt = c.exp_cnt;
+  j.exp_off = c.exp_off;
+  return j;
+}
+
+hipError_t launch_lists(const triroute_cfg &cfg, int B, int T, const uint8_t *mode,
+                        const int32_t *eidx, const triroute_compaction &c, int32_t *hist,
+                        bool attn_lists, const AppendJob *app, void *o, hipStream_t st) {
+  ListsArgs a{};
+  a.mode = mode;
+  a.eidx = eidx;
+  a.B = B;
+  a.T = T;
+  a.H = cfg.n_heads;
+  a.E1 = cfg.n_experts + 1;
+  a.Nk = B * T * cfg.top_k;
+  a.nattn = attn_lists ? B * a.H : 0;
+  a.nbe = (a.Nk + CHUNK - 1) / CHUNK;
+  a.attn_cnt = c.attn_cnt;
+  a.attn_idx = c.attn_idx;
+  a.hist = hist;
+  int zero_blocks = 0;
+  if (app) {
+    a.cv = app->cv;
+    a.seq_ids = app->seq_ids;
+    a.bit = app->bit;
+    a.old_len = app->ws.old_len;
+    a.nslot = app->slots ? B : 0;
+    if (o) {
+      const int64_t pairs = int64_t(B) * T * a.H;
+      a.chunks = cfg.head_dim * (cfg.act == TRIROUTE_BF16 ? 2 : 4) / 16;
+      if (pairs >= (int64_t(1) << 31)) {
+        const hipError_t e = launch_fill_u32(o, pairs * a.chunks * 4, 0u, st);  // every row
+        if (e != hipSuccess) return e;
+      } else {
+        a.o = (uint4 *)o;
+        a.pairs = uint32_t(pairs);
+        zero_blocks = int((pairs + 1023) / 1024);
+      }
+    }
+  }
+  lists_kernel<<<dim3(unsigned(a.nattn + a.nbe + a.nslot + zero_blocks)), 1024, 0, st>>>(a);
+  return hipGetLastError();
+}
+
+hipError_t launch_scatter(const ScatterJob &j, hipStream_t st) {
+  compact_scatter_kernel<<<j.nbe, 256, 0, st>>>(j);
+  return hipGetLastError();
+}
 
 hipError_t launch_compact(const triroute_cfg &cfg, int B, int T, const uint8_t *mode,
                           const int32_t *eidx, const triroute_compaction &c, int32_t *hist,
-                          hipStream_t st, bool attn_lists) {
-  const int H = cfg.n_heads, E1 = cfg.n_experts + 1, Nk = B * T * cfg.top_k;
-  const int nbe = (Nk + CHUNK - 1) / CHUNK;
-  if (!attn_lists && nbe == 1) {
-    compact_experts_one_kernel<<<1, 256, 0, st>>>(eidx, E1, Nk, c.exp_rows, c.exp_cnt, c.exp_off);
-    return hipGetLastError();
-  }
-  compact_count_kernel<<<B * H + nbe, 256, 0, st>>>(mode, eidx, B, T, H, E1, Nk, c.attn_cnt,
-                                                    c.attn_idx, hist);
-  compact_scatter_kernel<<<nbe, 256, 0, st>>>(eidx, hist, nbe, E1, Nk, c.exp_rows, c.exp_cnt,
-                                               c.exp_off);
-  return hipGetLastError();
+                          hipStream_t st) {
+  const hipError_t e = launch_lists(cfg, B, T, mode, eidx, c, hist, true, nullptr, nullptr, st);
+  if (e != hipSuccess) return e;
+  return launch_scatter(make_scatter_job(cfg, B * T, eidx, c, hist), st);
 }
 
 }  // namespace tr

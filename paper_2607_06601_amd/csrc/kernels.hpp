@@ -55,23 +55,50 @@ hipError_t launch_router(const triroute_cfg &cfg, int N, const void *x, const fl
                          hipStream_t st, TailTap tap = TailTap{});
 // compact.hip
 int compact_hist_ints(int N, int k, int E1);
-// attn_lists false: the attention lists are not wanted (decode reads the
-// modes themselves) and are left untouched.
+// The expert lists' second half: from the chunk histograms (or, for one chunk
+// beside an append of single tokens, from the choices alone) to the lists.
+struct ScatterJob {
+  const int32_t *eidx, *hist;
+  int nbe = 0, E1, Nk = 0;  // chunks of assignments, options, assignments
+  int32_t *rows, *exp_cnt, *exp_off;
+};
+ScatterJob make_scatter_job(const triroute_cfg &cfg, int N, const int32_t *eidx,
+                            const triroute_compaction &c, const int32_t *hist);
+hipError_t launch_scatter(const ScatterJob &j, hipStream_t st);
+struct AppendJob;
+// One launch: the attention lists (not in decode, which reads the modes
+// themselves: attn_lists false leaves them untouched), the expert histograms,
+// and, for a layer (app), the append's slots (app->slots) and the zeroed
+// attention rows of o (may be NULL).
+hipError_t launch_lists(const triroute_cfg &cfg, int B, int T, const uint8_t *mode,
+                        const int32_t *eidx, const triroute_compaction &c, int32_t *hist,
+                        bool attn_lists, const AppendJob *app, void *o, hipStream_t st);
+// both halves (the stage calls)
 hipError_t launch_compact(const triroute_cfg &cfg, int B, int T, const uint8_t *mode,
                           const int32_t *eidx, const triroute_compaction &c, int32_t *hist,
-                          hipStream_t st, bool attn_lists = true);
+                          hipStream_t st);
 // kv.hip
 hipError_t launch_fill_u32(void *p, int64_t n_words, uint32_t v, hipStream_t st);
 // append scratch: each row's pool lengths before the append
 struct KvWs {
   int32_t *old_len;  // [B][4]
 };
+struct AppendJob {
+  CacheView cv;
+  const int32_t *seq_ids;
+  const uint8_t *bit;
+  KvWs ws;
+  bool slots;  // several tokens a row: their slots are taken ahead of the codes
+};
+// launch_kv_append: slots_done: launch_lists took the slots; lists: expert
+// lists to make beside the append (T == 1: of one chunk, without histograms)
 // paged caches: fill the free stacks with every page; return a sequence's pages
 hipError_t launch_kv_paged_init(const CacheView &cv, const int32_t n_pages[4], hipStream_t st);
 hipError_t launch_kv_paged_reset(const CacheView &cv, int seq, hipStream_t st);
 hipError_t launch_kv_append(const triroute_cfg &cfg, const CacheView &cv, int B, int T,
                             const int32_t *seq_ids, const void *k, const void *v,
-                            const uint8_t *bit, const KvWs &ws, hipStream_t st);
+                            const uint8_t *bit, const KvWs &ws, hipStream_t st,
+                            bool slots_done = false, const ScatterJob *lists = nullptr);
 hipError_t launch_kv_export(const triroute_cfg &cfg, const CacheView &cv, int seq, int bi,
                             int slot0, int count, void *kout, void *vout, uint16_t *ksz,
                             uint16_t *vsz, int32_t *pos_out, hipStream_t st);

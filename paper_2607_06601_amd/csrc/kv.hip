@@ -5,7 +5,7 @@
 // mn/mx, s32 = (mx - mn) / (2^b - 1), s = fp16_rne(s32), z = fp16_rne(mn),
 // code = 0 if s == 0 else clamp(rint_even((x - z) / s), 0, 2^b - 1), every
 // step in IEEE fp32.  16-bit stores the activation value verbatim.
-#include "kernels.hpp"
+#include "lists.hpp"
 
 namespace tr {
 
@@ -23,101 +23,11 @@ hipError_t launch_fill_u32(void *p, int64_t n_words, uint32_t v, hipStream_t st)
   return hipGetLastError();
 }
 
-// Per batch row: the slot of each new token in its width pool (its rank
-// among the row's earlier tokens of that width, after the pool's current
-// length), its position in the pool's position array, the new lengths, and
-// the pool lengths before the append.  One block of 16 waves per row walks
-// the row's tokens 1024 at a time (ballot counts per wave, then per block).
 __global__ __launch_bounds__(1024) void kv_slots_kernel(CacheView cv, int T,
                                                         const int32_t *__restrict__ seq_ids,
                                                         const uint8_t *__restrict__ bit,
                                                         int32_t *__restrict__ old_len) {
-  constexpr int NW = 16;
-  __shared__ int wc[4][NW];
-  const int b = blockIdx.x;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int s = seq_ids ? seq_ids[b] : b;
-  if (s < 0 || s >= cv.n_seq) {
-    if (tid == 0) atomicOr(cv.status, int(TRIROUTE_CACHE_BAD_SEQ));
-    if (tid < 4) old_len[b * 4 + tid] = -1;
-    return;
-  }
-  const int len0 = cv.seq_len[s];
-  if (len0 + T > cv.capacity) {
-    if (tid == 0) atomicOr(cv.status, int(TRIROUTE_CACHE_OVERFLOW));
-    if (tid < 4) old_len[b * 4 + tid] = -1;
-    return;
-  }
-  int run[4];
-#pragma unroll
-  for (int bi = 0; bi < 4; ++bi) run[bi] = cv.pool_len[s * 4 + bi];
-  if (cv.PT) {
-    // paged: count the row's tokens per width, then take the pages the
-    // pools grow into from the free stacks (thread bi for width bi)
-    __shared__ int cnt_s[4], fail_s;
-    if (tid < 4) cnt_s[tid] = 0;
-    if (tid == 0) fail_s = 0;
-    __syncthreads();
-    for (int t0 = 0; t0 < T; t0 += 64 * NW) {
-      const int t = t0 + tid;
-      const int bi = t < T ? int(bit[int64_t(b) * T + t]) : -1;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const uint64_t bq = __ballot(bi == q);
-        if (lane == 0 && bq) atomicAdd(&cnt_s[q], __popcll(bq));  // a count: order does not matter
-      }
-    }
-    __syncthreads();
-    if (tid < 4) {
-      const int bi = tid, per = cv.PT * cv.TS;
-      const int need = (run[bi] + cnt_s[bi] + per - 1) / per;
-      int32_t *held = cv.alloc + s * 4 + bi;
-      const int have = *held;
-      if (need > have) {
-        const int k = need - have;
-        const int top = atomicSub(cv.free_top + bi, k);
-        if (need > cv.max_pages || top - k < 0) {
-          atomicAdd(cv.free_top + bi, k);  // give the claim back
-          atomicOr(&fail_s, 1);
-        } else {
-          for (int q = 0; q < k; ++q)
-            cv.page_table[(int64_t(s) * 4 + bi) * cv.max_pages + have + q] = cv.free_list[bi][top - k + q];
-          *held = need;
-        }
-      }
-    }
-    __syncthreads();
-    if (fail_s) {
-      if (tid == 0) atomicOr(cv.status, int(TRIROUTE_CACHE_OVERFLOW));
-      if (tid < 4) old_len[b * 4 + tid] = -1;
-      return;
-    }
-  }
-  if (tid < 4) old_len[b * 4 + tid] = run[tid];
-  for (int t0 = 0; t0 < T; t0 += 64 * NW) {
-    const int t = t0 + tid;
-    const int bi = t < T ? int(bit[int64_t(b) * T + t]) : -1;
-    uint64_t bal[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) bal[q] = __ballot(bi == q);
-    if (lane < 4) wc[lane][w] = __popcll(bal[lane]);
-    __syncthreads();
-    if (bi >= 0) {
-      int slot = run[bi] + __popcll(bal[bi] & lanemask_lt());
-      for (int ww = 0; ww < w; ++ww) slot += wc[bi][ww];
-      cv.pos_at(s, bi, slot) = len0 + t;
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int ww = 0; ww < NW; ++ww) run[q] += wc[q][ww];
-    __syncthreads();
-  }
-  if (tid == 0) {
-#pragma unroll
-    for (int bi = 0; bi < 4; ++bi) cv.pool_len[s * 4 + bi] = run[bi];
-    cv.seq_len[s] = len0 + T;
-  }
+  kv_slots_rows(cv, T, seq_ids, bit, old_len, blockIdx.x);
 }
 
 // One token per row (decode).  The slot of a row's token (sequence s, width
@@ -175,10 +85,15 @@ __global__ __launch_bounds__(256) void kv_token_kernel(CacheView cv,
                                                        const int32_t *__restrict__ seq_ids,
                                                        const T *__restrict__ kin,
                                                        const T *__restrict__ vin,
-                                                       const uint8_t *__restrict__ bit) {
+                                                       const uint8_t *__restrict__ bit,
+                                                       ScatterJob one) {
   __shared__ uint32_t kws[4][128];  // per wave: the token's K words (at most 4 dh bits / 32)
   __shared__ int slot_s;
-  const int i = blockIdx.x;  // row i = token i
+  int i = blockIdx.x;  // row i = token i
+  if (one.Nk > 0 && i-- == 0) {  // the step's expert lists, in a block of their own
+    experts_one(one);
+    return;
+  }
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int bi = __builtin_amdgcn_readfirstlane(int(bit[i]));
   const int s = seq_ids ? __builtin_amdgcn_readfirstlane(seq_ids[i]) : i;
@@ -483,10 +398,16 @@ __global__ __launch_bounds__(256) void kv_step_kernel(CacheView cv, int B, int T
                                                       const int32_t *__restrict__ seq_ids,
                                                       const T *__restrict__ kin,
                                                       const T *__restrict__ vin,
-                                                      const int32_t *__restrict__ old_len) {
+                                                      const int32_t *__restrict__ old_len,
+                                                      ScatterJob sc) {
+  // the first blocks, if any: the expert lists' chunks (sc.nbe of them)
+  if (int(blockIdx.x) < sc.nbe) {
+    scatter_chunk(sc, blockIdx.x);
+    return;
+  }
   __shared__ __align__(16) uint8_t stage_all[4][32 * DH * sizeof(T)];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  int u = __builtin_amdgcn_readfirstlane(int(blockIdx.x) * 4 + wave);
+  int u = __builtin_amdgcn_readfirstlane((int(blockIdx.x) - sc.nbe) * 4 + wave);
   const int j = u % JS;
   u /= JS;
   const int g = u % cv.Hkv;
@@ -616,24 +537,29 @@ hipError_t launch_kv_paged_reset(const CacheView &cv, int seq, hipStream_t st) {
 
 hipError_t launch_kv_append(const triroute_cfg &cfg, const CacheView &cv, int B, int T,
                             const int32_t *seq_ids, const void *k, const void *v,
-                            const uint8_t *bit, const KvWs &ws, hipStream_t st) {
+                            const uint8_t *bit, const KvWs &ws, hipStream_t st, bool slots_done,
+                            const ScatterJob *lists) {
+  ScatterJob job{};
+  if (lists) job = *lists;
   if (T == 1) {  // one token per row: slot and codes in one launch
+    const int rows = B + (lists ? 1 : 0);
     if (cfg.act == TRIROUTE_BF16)
-      kv_token_kernel<bf16><<<B, 256, 0, st>>>(cv, seq_ids, (const bf16 *)k, (const bf16 *)v, bit);
+      kv_token_kernel<bf16><<<rows, 256, 0, st>>>(cv, seq_ids, (const bf16 *)k, (const bf16 *)v, bit,
+                                                  job);
     else
-      kv_token_kernel<float><<<B, 256, 0, st>>>(cv, seq_ids, (const float *)k, (const float *)v,
-                                                bit);
+      kv_token_kernel<float><<<rows, 256, 0, st>>>(cv, seq_ids, (const float *)k, (const float *)v,
+                                                   bit, job);
     return hipGetLastError();
   }
-  kv_slots_kernel<<<B, 1024, 0, st>>>(cv, T, seq_ids, bit, ws.old_len);
+  if (!slots_done) kv_slots_kernel<<<B, 1024, 0, st>>>(cv, T, seq_ids, bit, ws.old_len);
   // 32-slot steps an append can touch in one pool: all T tokens, plus the
   // partly filled step it starts in
   const int JS = (T + 31) / 32 + 1;
   const int64_t units = int64_t(B) * 4 * cfg.n_kv_heads * JS;
-  const dim3 grid(unsigned((units + 3) / 4));
+  const dim3 grid(unsigned((units + 3) / 4) + unsigned(job.nbe));
   const int dh = cfg.head_dim, G = cfg.kv_group;
 #define KV_STEP(TT, DH_, G_) \
-  kv_step_kernel<TT, DH_, G_><<<grid, 256, 0, st>>>(cv, B, T, JS, seq_ids, (const TT *)k, (const TT *)v, ws.old_len)
+  kv_step_kernel<TT, DH_, G_><<<grid, 256, 0, st>>>(cv, B, T, JS, seq_ids, (const TT *)k, (const TT *)v, ws.old_len, job)
 #define KV_STEP_T(TT)                                  \
   do {                                                 \
     if (dh == 64) {                                    \

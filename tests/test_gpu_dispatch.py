@@ -433,3 +433,66 @@ def test_relaxed_backward_tiles(B, T, d, dpsi, H, E, k, groups, act):
     for n, t in out.items():
         if t.numel():
             assert_close(npy(t), npy(v[n[1:]].grad), "f32", n)
+
+
+# ------------------------------------------- lists and slots beside other work
+@pytest.mark.parametrize("B,T,prefill", [
+    (1, 1, False), (512, 1, False), (513, 1, False),   # decode: one chunk of 1024 assignments, two
+    (1, 1, True), (512, 1, True), (700, 1, True),      # prefill of single tokens, likewise
+    (3, 171, True), (2, 1030, True),                   # slots ahead of the codes, 1 and 2 rounds
+])
+def test_layer_lists_and_slots(monkeypatch, B, T, prefill):
+    """A layer's lists, slots and zeroed rows, made beside other kernels,
+    against the stage calls on the layer's own decisions: the same lists feed
+    the same kernels, so the results are the same bits; attention (split in
+    the layer's prefill) at the tolerance of its bf16 output."""
+    L = _small_layer(monkeypatch, B=B, T=T, H=4, Hkv=2, dh=64, w=100)
+    D = DeviceLayer(L)
+    c, N = D.cfg, B * T
+    caches = [tr.KVCache(c, B, T + 40) for _ in range(2)]
+    sid = torch.arange(B, dtype=torch.int32, device=DEV)
+    sid[1:][-1:] = B                             # the last of several rows is outside the cache
+    u8 = dict(dtype=torch.uint8, device=DEV)
+
+    def act(*shape):
+        return torch.full(shape, float("nan"), dtype=D.act, device=DEV)
+
+    t = dict(q=act(N, 256), k=act(N, 128), v=act(N, 128), o=act(N, 256), xt=act(N, 256),
+             mode=torch.empty(N, 4, **u8), bit=torch.empty(N, **u8),
+             eidx=torch.empty(N, 2, dtype=torch.int32, device=DEV),
+             egate=torch.empty(N, 2, device=DEV))
+    x_out = act(N, 256)
+    args = (B, T) if prefill else (B,)
+    run, op = (tr.layer_prefill, tr.OP_LAYER_PREFILL) if prefill else \
+        (tr.layer_decode, tr.OP_LAYER_DECODE)
+    ws = tr.workspace(c, op, B, T)
+    ws.fill_(0xFF)
+    print(f"lists B={B} T={T} prefill={prefill}", flush=True)
+    run(c, *args, D.x, D.psi, D.rw, D.dw, D.mw, caches[0], x_out, ws,
+        taps=tr.Taps(**{n: v.data_ptr() for n, v in t.items()}), seq_ids=sid)
+    cmp = tr.CompactionBuffers(c, B, T)
+    mode, bit, eidx = (torch.empty_like(t[n]) for n in ("mode", "bit", "eidx"))
+    tr.router(c, B, T, D.x, D.psi, D.rw, act(N, 256), mode, bit, eidx,
+              torch.empty(N, 2, device=DEV), cmp.struct, tr.workspace(c, tr.OP_ROUTER, B, T))
+    tr.kv_append(c, caches[1], B, T, t["k"], t["v"], bit, tr.workspace(c, tr.OP_KV_APPEND, B, T),
+                 seq_ids=sid)
+    o, y = act(N, 256), act(N, 256)
+    if prefill:
+        tr.attn_prefill(c, B, T, t["q"], caches[1], mode, cmp.struct, o, seq_ids=sid)
+    else:
+        tr.attn_decode(c, B, t["q"], caches[1], mode, o,
+                       ws=tr.workspace(c, tr.OP_ATTN_DECODE, B, 1), seq_ids=sid)
+    tr.moe(c, N, t["xt"], D.dw, D.mw, eidx, t["egate"], cmp.struct, y,
+           tr.workspace(c, tr.OP_MOE, B, T))
+    torch.cuda.synchronize()
+    for n, v in (("mode", mode), ("bit", bit), ("eidx", eidx)):
+        assert torch.equal(t[n], v), n
+    assert torch.equal(x_out, y)
+    assert torch.equal(caches[0].seq_len(), caches[1].seq_len())
+    assert torch.equal(caches[0].pool_len(), caches[1].pool_len())
+    assert caches[0].status() == caches[1].status() == (tr.CACHE_BAD_SEQ if B > 1 else 0)
+    assert_close(npy(t["o"]), npy(o), "bf16", "o")
+    zero = (t["mode"] == 0)
+    if B > 1:
+        zero[-T:] = True
+    assert not t["o"].view(N, 4, 64)[zero].any()
