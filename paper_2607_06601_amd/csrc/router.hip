@@ -166,217 +166,264 @@ __global__ __launch_bounds__(256) void trunk1_kernel(const T *__restrict__ x,
   }
 }
 
-// Tail in 16-token tiles (4 waves per tile, fp32 MFMA 16x16x4), two tiles
-// at a time per block (8 waves: two per SIMD, so one tile's latencies hide
-// behind the other's work), with W2 and the head weights staged in LDS once
-// by coalesced loads:
+// Tail, a tile of TB <= 16 tokens a block of four waves:
 //   u = GELU(sum of trunk partials + b1); h = W2 u + b2; h^ = RMSNorm(h) gr;
 //   z = [Wa; We; Wb] h^ + [ca; ce; cb]; argmax / top-k decisions and gates.
-constexpr int RT_TB = 16, RT_DR = 128, RT_LD = RT_DR + 1, RT_NZ = 112;
-constexpr size_t RT_LDS = sizeof(float) * (size_t(RT_DR + RT_NZ + 4 * RT_TB) * RT_LD);
+// A chain of short steps, so its length counts and not its arithmetic.  The
+// products are taken transposed (fp32 MFMA 16x16x4, weight rows by tokens):
+// wave w owns rows 32 w .. 32 w + 31 of W2 and the logit tiles w, w + 4, ...,
+// and holds them in registers as the MFMA wants them (four consecutive inputs
+// a lane; one 16-byte load feeds four steps), fetched from L2 before anything
+// waits for the trunk.  A lane then has four consecutive outputs of one token:
+// the norm is two shuffles and an exchange of four sums, and h^ and z go to LDS
+// in 16 bytes.  Few blocks' worth of tokens are spread over the chip in
+// smaller tiles (launch_router); the columns past TB hold whatever the LDS
+// held, which no other column reads, and are not stored.  With fewer than 8
+// tokens the trunk's chunks are summed by 8 / TB groups of threads, a run of
+// chunks each, whose sums are added in order.
+// (Weights staged in LDS by blocks of eight waves, a CU each: 20.7 us at 333
+// tokens, 24 at 512 of the 1.3B layer, 38 at 16384; so: 10, 12.9, 25.4.  A
+// prefill of 333 tokens at 410M 152 -> 139 us, of 512 at 1.3B 727 -> 700.)
+constexpr int RT_TB = 16, RT_DR = 128, RT_NZ = 112, RT_TILES = 256;
+constexpr int RT_LD = RT_DR + 4, RT_ZLD = RT_NZ + 4;
 
-__global__ __launch_bounds__(512) void router_tail_kernel(
+template <bool TWO>  // 16 tokens: two float4 of u a thread, several tiles a block
+__global__ __launch_bounds__(256, 2) void router_tail_kernel(
     const float *__restrict__ upart, int KS, const float *__restrict__ b1,
     const float *__restrict__ W2, const float *__restrict__ b2, const float *__restrict__ gr,
     const float *__restrict__ Wa, const float *__restrict__ ca, const float *__restrict__ We,
     const float *__restrict__ ce, const float *__restrict__ Wb, const float *__restrict__ cb,
     uint8_t *__restrict__ mode, uint8_t *__restrict__ bit, int32_t *__restrict__ eidx,
-    float *__restrict__ egate, int N, int H, int A, int E1, int k, float eps, TailTap tap) {
-  constexpr int TB = RT_TB, DR = RT_DR, LD = RT_LD;
-  extern __shared__ __align__(16) float rt_lds[];
-  float(*W2s)[LD] = (float(*)[LD])rt_lds;              // [128][LD]
-  float(*Wzs)[LD] = (float(*)[LD])(rt_lds + DR * LD);  // [NZ][LD]
-  // group g of 4 waves works on its own tile with its own Us / Zs
-  const int g = threadIdx.x >> 8, tid = threadIdx.x & 255, lane = tid & 63, wave = tid >> 6;
-  float(*Us)[LD] = (float(*)[LD])(rt_lds + (DR + RT_NZ + 2 * TB * g) * LD);
-  float(*Zs)[LD] = (float(*)[LD])(rt_lds + (DR + RT_NZ + 2 * TB * g + TB) * LD);
+    float *__restrict__ egate, int N, int TB, int H, int A, int E1, int k, float eps,
+    TailTap tap) {
+  constexpr int DR = RT_DR, NE = TWO ? 2 : 1, NB = TWO ? 2 : 12;
+  __shared__ __align__(16) float Us[RT_TB][RT_LD];   // u, then h^
+  __shared__ __align__(16) float Zs[RT_TB][RT_ZLD];  // the groups' chunk sums, then z
+  __shared__ __align__(16) float b2s[DR], grs[DR], bzs[RT_NZ];
+  __shared__ float red[4][RT_TB];
+  static_assert(8 * RT_LD <= RT_TB * RT_ZLD, "chunk sums fit");
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tl = lane & 15, q4 = (lane >> 4) * 4;
   const int NZ = 3 * A + E1 + 4;
-  for (int i = threadIdx.x; i < DR * DR / 4; i += 512) {
-    const int r = i / (DR / 4), c4 = (i % (DR / 4)) * 4;
-    const float4 v = *(const float4 *)(W2 + r * DR + c4);
-    W2s[r][c4] = v.x; W2s[r][c4 + 1] = v.y; W2s[r][c4 + 2] = v.z; W2s[r][c4 + 3] = v.w;
-  }
-  for (int i = threadIdx.x; i < NZ * DR / 4; i += 512) {
-    const int z = i / (DR / 4), c4 = (i % (DR / 4)) * 4;
-    const float *wz = z < 3 * A ? Wa + z * DR
-                      : z < 3 * A + E1 ? We + (z - 3 * A) * DR : Wb + (z - 3 * A - E1) * DR;
-    const float4 v = *(const float4 *)(wz + c4);
-    Wzs[z][c4] = v.x; Wzs[z][c4 + 1] = v.y; Wzs[z][c4 + 2] = v.z; Wzs[z][c4 + 3] = v.w;
-  }
-  // the weights stay in LDS while the block walks its token tiles; with at
-  // most 4 trunk chunks the next tile's partials are loaded while the
-  // current tile is computed
-  constexpr int EPT = TB * DR / 256;
-  float pre[4][EPT];
-  auto load_parts = [&](int tt0, int s0, float (*v)[EPT]) {
+  auto zrow = [&](int z) {
+    z = z < NZ ? z : NZ - 1;
+    return z < 3 * A ? Wa + z * DR : z < 3 * A + E1 ? We + (z - 3 * A) * DR
+                                                    : Wb + (z - 3 * A - E1) * DR;
+  };
+  // element (token ut, columns uc ..), group ug of the NG that share the chunks
+  const int nel = 32 * (TB < 8 ? TB : 8), NG = 256 / nel;
+  const int ut = (tid & (nel - 1)) >> 5, uc = (tid & 31) * 4, ug = tid / nel;
+  const int per = (KS + NG - 1) / NG, sb = ug * per, se = min(KS, sb + per);
+  f32x4r pre[NB][NE];
+  auto load_parts = [&](int t0, int s0) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int s = 0; s < NB; ++s)
 #pragma unroll
-      for (int e = 0; e < EPT; ++e) {
-        const int idx = tid + 256 * e, t = idx / DR, c = idx % DR;
-        v[j][e] = (s0 + j < KS && tt0 + t < N)
-                      ? upart[(int64_t(s0 + j) * N + tt0 + t) * DR + c] : 0.f;
+      for (int e = 0; e < NE; ++e) {
+        pre[s][e] = f32x4r{0.f, 0.f, 0.f, 0.f};
+        if (s0 + s < se && ut + 8 * e < min(TB, N - t0))
+          pre[s][e] = *(const f32x4r *)(upart + (int64_t(s0 + s) * N + t0 + ut + 8 * e) * DR + uc);
       }
   };
-  const bool prefetch = KS <= 4;
-  // both groups run every round (a group past the last token masks its
-  // work), so the block's barriers stay matched
-  const int stride = gridDim.x * 2 * TB;
-  if (prefetch) load_parts(blockIdx.x * 2 * TB + g * TB, 0, pre);
-  for (int base = blockIdx.x * 2 * TB; base < N; base += stride) {
-  const int t0 = base + g * TB;
+  // loads in the order in which they are waited for: the trunk's chunks, the
+  // small vectors, the weights
+  load_parts(blockIdx.x * TB, sb);
+  __builtin_amdgcn_sched_barrier(0);
+  const f32x4r b1v = {b1[uc], b1[uc + 1], b1[uc + 2], b1[uc + 3]};
+  float sv[3] = {0.f, 0.f, 0.f};
+  if (tid < DR) {
+    sv[0] = b2[tid];
+    sv[1] = gr[tid];
+    if (tid < NZ) sv[2] = tid < 3 * A ? ca[tid] : tid < 3 * A + E1 ? ce[tid - 3 * A]
+                                                                   : cb[tid - 3 * A - E1];
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  f32x4r w2[2][8], wz[8], wx[8];
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int s = 0; s < 8; ++s)
+      w2[j][s] = *(const f32x4r *)(W2 + (32 * wave + 16 * j + tl) * DR + 16 * s + q4);
   {
-    // u = GELU(sum of the KS trunk partials + b1): thread tid owns elements
-    // tid + 256 e of the block's 16 x 128; partials are summed in chunk order
-    float sacc[EPT];
+    const float *row = zrow(16 * wave + tl);
 #pragma unroll
-    for (int e = 0; e < EPT; ++e) sacc[e] = 0.f;
-    if (prefetch) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int e = 0; e < EPT; ++e) sacc[e] += pre[j][e];
-      if (t0 + stride < N) load_parts(t0 + stride, 0, pre);
-    } else {
-      for (int s0 = 0; s0 < KS; s0 += 4) {
-        float v[4][EPT];
-        load_parts(t0, s0, v);
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-          for (int e = 0; e < EPT; ++e) sacc[e] += v[j][e];
-      }
-    }
-#pragma unroll
-    for (int e = 0; e < EPT; ++e) {
-      const int idx = tid + 256 * e, t = idx / DR, c = idx % DR;
-      float y = 0.f;
-      if (t0 + t < N) {
-        y = sacc[e] + b1[c];
-        if (tap.a1) tap.a1[int64_t(t0 + t) * DR + c] = y;
-        y = 0.5f * y * (1.0f + erff(y * 0.70710678118654752f));
-      }
-      Us[t][c] = y;
-    }
+    for (int s = 0; s < 8; ++s) wz[s] = *(const f32x4r *)(row + 16 * s + q4);
   }
-  __syncthreads();
-  // h: wave w computes columns 32 w .. 32 w + 31 (two accumulators per
-  // column tile, even and odd K steps, so that two MFMA chains interleave)
-  f32x4r hacc[2][2];
-#pragma unroll
-  for (int j = 0; j < 2; ++j) hacc[j][0] = hacc[j][1] = f32x4r{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 8
-  for (int kk = 0; kk < DR; kk += 4) {
-    const float av = Us[lane & 15][kk + (lane >> 4)];
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-      hacc[j][(kk >> 2) & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(
-          av, W2s[32 * wave + 16 * j + (lane & 15)][kk + (lane >> 4)], hacc[j][(kk >> 2) & 1], 0,
-          0, 0);
+  __builtin_amdgcn_sched_barrier(0);
+  if (tid < DR) {  // read behind the loop's first barrier
+    b2s[tid] = sv[0];
+    grs[tid] = sv[1];
+    if (tid < RT_NZ) bzs[tid] = sv[2];
   }
-  __syncthreads();
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int n = 32 * wave + 16 * j + (lane & 15);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const float hv = (hacc[j][0][r] + hacc[j][1][r]) + b2[n];
-      Us[4 * (lane >> 4) + r][n] = hv;
-      const int tr_ = t0 + 4 * (lane >> 4) + r;
-      if (tap.hpre && tr_ < N) tap.hpre[int64_t(tr_) * DR + n] = hv;
-    }
-  }
-  __syncthreads();
-  {
-    // RMSNorm of h: wave w takes tokens w, w + 4, w + 8, w + 12 together
-    constexpr int TPW = TB / 4;
-    float av[TPW], bv[TPW], ss[TPW];
-#pragma unroll
-    for (int j = 0; j < TPW; ++j) {
-      av[j] = Us[wave + 4 * j][lane];
-      bv[j] = Us[wave + 4 * j][lane + 64];
-      ss[j] = av[j] * av[j] + bv[j] * bv[j];
-    }
-#pragma unroll
-    for (int j = 0; j < TPW; ++j) ss[j] = seg_sum(ss[j], 64);
-#pragma unroll
-    for (int j = 0; j < TPW; ++j) {
-      const float r = 1.0f / sqrtf(ss[j] / float(DR) + eps);
-      Us[wave + 4 * j][lane] = (av[j] * r) * gr[lane];
-      Us[wave + 4 * j][lane + 64] = (bv[j] * r) * gr[lane + 64];
-      const int tj = t0 + wave + 4 * j;
-      if (tap.h && tj < N) {
-        tap.h[int64_t(tj) * DR + lane] = Us[wave + 4 * j][lane];
-        tap.h[int64_t(tj) * DR + lane + 64] = Us[wave + 4 * j][lane + 64];
-      }
-    }
-  }
-  __syncthreads();
-  for (int nt = wave; nt * 16 < NZ; nt += 4) {
-    const int z = nt * 16 + (lane & 15);
-    const int zr = z < NZ ? z : NZ - 1;
-    f32x4r zacc[2] = {f32x4r{0.f, 0.f, 0.f, 0.f}, f32x4r{0.f, 0.f, 0.f, 0.f}};
-#pragma unroll 8
-    for (int kk = 0; kk < DR; kk += 4)
-      zacc[(kk >> 2) & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(
-          Us[lane & 15][kk + (lane >> 4)], Wzs[zr][kk + (lane >> 4)], zacc[(kk >> 2) & 1], 0, 0, 0);
-    if (z < NZ) {
-      const float bias = z < 3 * A ? ca[z] : z < 3 * A + E1 ? ce[z - 3 * A] : cb[z - 3 * A - E1];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) Zs[4 * (lane >> 4) + r][z] = (zacc[0][r] + zacc[1][r]) + bias;
-    }
-  }
-  __syncthreads();
-  if (tap.z)
-    for (int it = tid; it < TB * NZ; it += 256) {
-      const int tt = it / NZ, z = it - tt * NZ;
-      if (t0 + tt < N) tap.z[int64_t(t0 + tt) * NZ + z] = Zs[tt][z];
-    }
-  // modes: one thread per (token, head); argmax, first maximum on ties
   const int HA = H / A;  // heads per decision group
-  for (int it = tid; it < TB * H; it += 256) {
-    const int tt = it / H, hh = it - tt * H;
-    if (t0 + tt >= N) continue;
-    const float *za = Zs[tt] + 3 * (hh / HA);
-    int best = 0;
-    if (za[1] > za[best]) best = 1;
-    if (za[2] > za[best]) best = 2;
-    mode[int64_t(t0 + tt) * H + hh] = uint8_t(best);
-  }
-  // bit width and experts: wave w takes tokens w, w + 4, ...; lane j holds
-  // expert logit j (E + 1 <= 64)
-  for (int tt = wave; tt < TB; tt += 4) {
-    const int t = t0 + tt;
-    if (t >= N) break;  // wave-uniform
-    const float *z = Zs[tt];
-    if (lane == 0) {
-      const float *zb = z + 3 * A + E1;
-      int bb = 0;
-      for (int j = 1; j < 4; ++j)
-        if (zb[j] > zb[bb]) bb = j;
-      bit[t] = uint8_t(bb);
+  for (int t0 = blockIdx.x * TB; t0 < N; t0 += gridDim.x * TB) {
+    const int nt = min(TB, N - t0);  // this tile's tokens
+    f32x4r u[NE];
+#pragma unroll
+    for (int e = 0; e < NE; ++e) u[e] = f32x4r{0.f, 0.f, 0.f, 0.f};
+    for (int s0 = sb;;) {
+#pragma unroll
+      for (int s = 0; s < NB; ++s)
+#pragma unroll
+        for (int e = 0; e < NE; ++e) u[e] += pre[s][e];
+      s0 += NB;
+      if (s0 >= se) break;
+      load_parts(t0, s0);
     }
-    // top-k by logit (softmax is monotone), ties to the lower id; the gate
-    // renormalises over the selected set, null included
-    const float zj = lane < E1 ? z[3 * A + lane] : -INFINITY;
-    const float zmax = seg_max(zj, 64);
-    uint64_t taken = 0;
-    float tot = 0.f;
-    for (int sl = 0; sl < k; ++sl) {
-      const float cand = (lane < E1 && !(taken >> lane & 1)) ? zj : -INFINITY;
-      const float m = seg_max(cand, 64);
-      const uint64_t hit = __ballot(lane < E1 && !(taken >> lane & 1) && cand == m);
-      const int best = __ffsll((unsigned long long)hit) - 1;
-      taken |= 1ull << best;
-      tot += expf(m - zmax);
+    if (TWO && t0 + int(gridDim.x) * TB < N) load_parts(t0 + gridDim.x * TB, sb);
+    if (!TWO && NG > 1) {  // (block-uniform)
+      float *ps = &Zs[0][0];
+      *(f32x4r *)(ps + (ug * TB + ut) * RT_LD + uc) = u[0];
+      __syncthreads();
+      if (ug == 0)
+        for (int g = 1; g < NG; ++g) u[0] += *(const f32x4r *)(ps + (g * TB + ut) * RT_LD + uc);
     }
-    if (taken >> lane & 1) {
-      const int sl = __popcll(taken & lanemask_lt());
-      eidx[int64_t(t) * k + sl] = lane;
-      egate[int64_t(t) * k + sl] = expf(zj - zmax) / tot;
+    if (ug == 0) {
+#pragma unroll
+      for (int e = 0; e < NE; ++e) {
+        f32x4r a = u[e] + b1v, y;
+        if (tap.a1 && ut + 8 * e < nt)
+          *(f32x4r *)(tap.a1 + int64_t(t0 + ut + 8 * e) * DR + uc) = a;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) y[i] = 0.5f * a[i] * (1.0f + erff(a[i] * 0.70710678118654752f));
+        *(f32x4r *)&Us[ut + 8 * e][uc] = y;
+      }
     }
-  }
-  __syncthreads();  // Us / Zs are reused by the next tile
+    __syncthreads();
+    // h: two accumulators per 16 rows (even and odd steps)
+    f32x4r hv[2];
+    {
+      f32x4r acc[2][2];
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[j][0] = acc[j][1] = f32x4r{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s = 0; s < 8; ++s) {
+        const f32x4r x = *(const f32x4r *)&Us[tl][16 * s + q4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+            acc[j][i & 1] =
+                __builtin_amdgcn_mfma_f32_16x16x4f32(w2[j][s][i], x[i], acc[j][i & 1], 0, 0, 0);
+      }
+      if (16 * wave + 64 < NZ) {  // the wave's second logit tile, on its way meanwhile
+        const float *row = zrow(16 * wave + 64 + tl);
+#pragma unroll
+        for (int s = 0; s < 8; ++s) wx[s] = *(const f32x4r *)(row + 16 * s + q4);
+      }
+      float ss = 0.f;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        hv[j] = (acc[j][0] + acc[j][1]) + *(const f32x4r *)(b2s + 32 * wave + 16 * j + q4);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) ss = fmaf(hv[j][r], hv[j][r], ss);
+      }
+      ss += __shfl_xor(ss, 16, 64);
+      ss += __shfl_xor(ss, 32, 64);
+      if (lane < 16) red[wave][lane] = ss;
+    }
+    __syncthreads();
+    {
+      const float ss = (red[0][tl] + red[1][tl]) + (red[2][tl] + red[3][tl]);
+      const float r = 1.0f / sqrtf(ss / float(DR) + eps);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int n = 32 * wave + 16 * j + q4;
+        const f32x4r hn = (hv[j] * r) * *(const f32x4r *)(grs + n);
+        *(f32x4r *)&Us[tl][n] = hn;
+        if (tl < nt) {
+          if (tap.hpre) *(f32x4r *)(tap.hpre + int64_t(t0 + tl) * DR + n) = hv[j];
+          if (tap.h) *(f32x4r *)(tap.h + int64_t(t0 + tl) * DR + n) = hn;
+        }
+      }
+    }
+    __syncthreads();
+    auto logits = [&](int zt, const f32x4r *w) {
+      f32x4r acc[2];
+      acc[0] = acc[1] = f32x4r{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s = 0; s < 8; ++s) {
+        const f32x4r x = *(const f32x4r *)&Us[tl][16 * s + q4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          acc[i & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[s][i], x[i], acc[i & 1], 0, 0, 0);
+      }
+      *(f32x4r *)&Zs[tl][16 * zt + q4] =
+          (acc[0] + acc[1]) + *(const f32x4r *)(bzs + 16 * zt + q4);
+    };
+    static_assert(RT_NZ <= 128, "two logit tiles a wave");
+    if (16 * wave < NZ) logits(wave, wz);  // (wave-uniform, no barrier inside)
+    if (16 * wave + 64 < NZ) logits(wave + 4, wx);
+    __syncthreads();
+    if (tap.z)
+      for (int it = tid; it < nt * NZ; it += 256) {
+        const int tt = it / NZ, z = it - tt * NZ;
+        tap.z[int64_t(t0) * NZ + it] = Zs[tt][z];
+      }
+    // decisions: 16 lanes per token.  Modes: heads j, j + 16, ...; argmax, first
+    // maximum on ties.  Bit width and experts: lane j holds expert logits j,
+    // j + 16, ... (E + 1 <= 64)
+    if (4 * wave < nt) {  // wave-uniform
+      const int tt = 4 * wave + (lane >> 4);
+      const float *z = Zs[tt], *ze = z + 3 * A;
+      const bool live = tt < nt;
+      const int64_t t = t0 + tt;
+      if (live)
+        for (int hh = tl; hh < H; hh += 16) {
+          const float *za = z + 3 * (HA == 1 ? hh : hh / HA);
+          int best = 0;
+          if (za[1] > za[best]) best = 1;
+          if (za[2] > za[best]) best = 2;
+          mode[t * H + hh] = uint8_t(best);
+        }
+      if (live && tl == 0) {
+        const float *zb = ze + E1;
+        const float z0 = zb[0], z1 = zb[1], z2 = zb[2], z3 = zb[3];
+        int bb = z1 > z0 ? 1 : 0;
+        float zm = z1 > z0 ? z1 : z0;
+        if (z2 > zm) { bb = 2; zm = z2; }
+        if (z3 > zm) bb = 3;
+        bit[t] = uint8_t(bb);
+      }
+      // top-k by logit (softmax is monotone), ties to the lower id; the gate
+      // renormalises over the selected set, null included
+      float zj[4], zmax = -INFINITY;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        zj[q] = 16 * q + tl < E1 ? ze[16 * q + tl] : -INFINITY;
+        zmax = fmaxf(zmax, zj[q]);
+      }
+      zmax = seg_max(zmax, 16);
+      uint64_t open = E1 < 64 ? (1ull << E1) - 1 : ~0ull, all = open;  // not yet taken
+      float tot = 0.f;
+      for (int sl = 0; sl < k; ++sl) {
+        float m = -INFINITY;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (open >> (16 * q + tl) & 1) m = fmaxf(m, zj[q]);
+        m = seg_max(m, 16);
+        uint64_t hit = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (16 * q < E1)  // uniform
+            hit |= (__ballot(zj[q] == m) >> (lane & 48) & 0xffffull) << (16 * q);
+        hit &= open;
+        if (!hit) hit = open;  // only NaNs left: the lowest id
+        open &= ~(hit & (~hit + 1));
+        tot += expf(m - zmax);
+      }
+      const uint64_t taken = all & ~open;
+      if (live)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (taken >> (16 * q + tl) & 1) {
+            const int sl = __popcll(taken & ((1ull << (16 * q + tl)) - 1));
+            eidx[t * k + sl] = 16 * q + tl;
+            egate[t * k + sl] = expf(zj[q] - zmax) / tot;
+          }
+    }
+    if (!TWO) return;
+    __syncthreads();  // the next tile writes Us and Zs
   }
 }
 
@@ -529,18 +576,24 @@ hipError_t launch_router(const triroute_cfg &cfg, int N, const void *x, const fl
     trunk1_kernel<float><<<g2, 256, 0, st>>>((const float *)x, rinv, w.g1, psi, w.W1, u, N, d,
                                              cfg.d_psi, kchunk);
   }
-  if (N <= 256 && ks <= RTB_MAXKS) {  // few tokens: one block per token
+  if (N <= 256 && ks <= RTB_MAXKS) {  // a CU a token, where the vector units are the shorter way:
+    // the same layers with the tiles of one token instead, 160M decode of one
+    // row 68.0 -> 68.8 us, 410M of 32 rows 128.0 -> 128.6, fp32 of 17 83.4 -> 84.6
     router_tail_blk_kernel<<<dim3(N), 256, 0, st>>>(
         u, ks, w.b1, w.W2, w.b2, w.gr, w.Wa, w.ca, w.We, w.ce, w.Wb, w.cb, mode, bit, eidx, egate,
         N, cfg.n_heads, attn_groups(cfg), cfg.n_experts + 1, cfg.top_k, cfg.rms_eps, tap);
     return hipGetLastError();
   }
-  // one block per CU at most (the weights fill most of its LDS), each
-  // loading them once and then taking every 256th token tile
-  const int pairs = ((N + RT_TB - 1) / RT_TB + 1) / 2;
-  router_tail_kernel<<<dim3(pairs < 256 ? pairs : 256), 512, RT_LDS, st>>>(
+  // tokens per tile: the fewest (a power of two) whose tiles are at most one a
+  // CU; past 8192 tokens the
+  // two blocks a CU that its registers allow keep their weights for several
+  int tb = 1;
+  while (tb < RT_TB && (N + tb - 1) / tb > RT_TILES) tb *= 2;
+  const int tiles = (N + tb - 1) / tb;
+  auto *tail = tb == RT_TB ? router_tail_kernel<true> : router_tail_kernel<false>;
+  tail<<<dim3(tiles < 512 ? tiles : 512), 256, 0, st>>>(
       u, ks, w.b1, w.W2, w.b2, w.gr, w.Wa, w.ca, w.We, w.ce, w.Wb, w.cb, mode, bit, eidx, egate, N,
-      cfg.n_heads, attn_groups(cfg), cfg.n_experts + 1, cfg.top_k, cfg.rms_eps, tap);
+      tb, cfg.n_heads, attn_groups(cfg), cfg.n_experts + 1, cfg.top_k, cfg.rms_eps, tap);
   return hipGetLastError();
 }
 

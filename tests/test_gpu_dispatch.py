@@ -496,3 +496,72 @@ def test_layer_lists_and_slots(monkeypatch, B, T, prefill):
     if B > 1:
         zero[-T:] = True
     assert not t["o"].view(N, 4, 64)[zero].any()
+
+
+# --------------------------------------------------------- controller's tail
+@pytest.mark.parametrize("N,d,H,E,k,groups", [
+    (1, 128, 2, 1, 1, 0), (256, 128, 4, 4, 1, 2),      # the form for few tokens
+    (3, 3136, 16, 16, 2, 0),                           # its chunks are too many: tiles of one
+    (257, 1024, 16, 16, 2, 0), (1000, 128, 4, 63, 5, 0),  # 2 and 4; 69 logits; 64 options
+    (2048, 128, 30, 12, 13, 0), (2049, 128, 12, 8, 2, 1),  # 8, 107 logits, all taken; 16
+    (8192, 128, 12, 8, 2, 0), (8193, 128, 12, 8, 2, 0),    # a tile a block; a block with two
+    (24600, 128, 32, 4, 2, 16),                        # four tiles a block, heads past 16
+])
+def test_router_tail_tiles(N, d, H, E, k, groups):
+    """The logits on both sides of the tail's tile rule against fp64, within
+    the fp32 bound, and the decisions against the call's own logits: first
+    maximum on ties (planted), gates within the rounding of k + 2 terms."""
+    A, dev = groups or H, dict(device=DEV)
+    c = tr.make_cfg(d, H, H // 2, 64, 64, E, k, 128, 64, "f32", d_psi=8, attn_groups=groups)
+    g = torch.Generator(**dev)
+    g.manual_seed(81)
+
+    def rnd(*shape, std=1.0):
+        return torch.randn(shape, generator=g, **dev) * std
+
+    w = dict(g1=1 + rnd(d, std=0.02), W1=rnd(128, d + 8, std=0.6 * d ** -0.5), b1=rnd(128, std=0.02),
+             W2=rnd(128, 128, std=0.1), b2=rnd(128, std=0.02), gr=1 + rnd(128, std=0.02),
+             Wa=rnd(3 * A, 128, std=0.1), ca=rnd(3 * A, std=0.1), We=rnd(E + 1, 128, std=0.1),
+             ce=rnd(E + 1, std=0.1), Wb=rnd(4, 128, std=0.1), cb=rnd(4, std=0.1))
+    for m, b, i, j in (("Wa", "ca", 0, 2), ("We", "ce", 0, E), ("Wb", "cb", 1, 3)):  # equal logits
+        w[m][j], w[b][j] = w[m][i].clone(), w[b][i].clone()
+    rw = tr.RouterW(*(t.data_ptr() for t in w.values()))
+    x, psi = rnd(N, d), rnd(N, 8)
+    pos = torch.arange(N, dtype=torch.int32, **dev)
+    ga, gb = rnd(N, A, 3), rnd(N, 4)
+    p = tr.RelaxParams(g_attn=ga.data_ptr(), g_bits=gb.data_ptr(), pos=pos.data_ptr(), tau_a=1.3,
+                       tau_b=0.8, zeta=0.99, alpha=0.01, beta=0.001, gamma=0.1)
+    f64 = dict(dtype=torch.float64, **dev)
+    z = torch.full((N, 3 * A + E + 5), float("nan"), **dev)
+    o = dict(y_attn=torch.empty(N, A, 3, **dev), y_bits=torch.empty(N, 4, **dev),
+             c_flops=torch.empty(N, **dev), c_mem=torch.empty(N, **dev), z=z,
+             stats=torch.empty(tr.RELAX_NSTAT, **f64), usage_exp=torch.empty(2, E + 1, **f64))
+    u8 = dict(dtype=torch.uint8, **dev)
+    cmp = tr.CompactionBuffers(c, 1, N)
+    mode, bit = torch.full((N, H), 9, **u8), torch.full((N,), 9, **u8)
+    eidx, egate = torch.full((N, k), -1, dtype=torch.int32, **dev), torch.empty(N, k, **dev)
+    print(f"router tail N={N} d={d} H={H} E={E} k={k}", flush=True)
+    tr.router_relaxed(c, 1, N, x, psi, rw, p, torch.empty_like(x), torch.empty_like(mode),
+                      torch.empty_like(bit), torch.empty_like(eidx), torch.empty_like(egate),
+                      cmp.struct, tr.RelaxOut(**{n: t.data_ptr() for n, t in o.items()}),
+                      tr.workspace(c, tr.OP_ROUTER_RELAXED, 1, N))
+    ws = tr.workspace(c, tr.OP_ROUTER, 1, N)
+    ws.fill_(0xFF)
+    tr.router(c, 1, N, x, psi, rw, torch.empty_like(x), mode, bit, eidx, egate, cmp.struct, ws)
+    torch.cuda.synchronize()
+    v = {n: t.double() for n, t in dict(w, x=x, psi=psi).items()}
+    n1 = v["x"] * torch.rsqrt(v["x"].square().mean(1, keepdim=True) + 1e-6) * v["g1"]
+    a1 = torch.cat([n1, v["psi"]], 1) @ v["W1"].t() + v["b1"]
+    h = (0.5 * a1 * (1 + torch.erf(a1 / 2 ** 0.5))) @ v["W2"].t() + v["b2"]
+    h = h * torch.rsqrt(h.square().mean(1, keepdim=True) + 1e-6) * v["gr"]
+    ref = torch.cat([h @ v["W" + n].t() + v["c" + n] for n in "aeb"], 1)
+    assert_close(npy(z), npy(ref), "f32", "z")
+    za, ze, zb = npy(z)[:, :3 * A].reshape(N, A, 3), npy(z)[:, 3 * A:-4], npy(z)[:, -4:]
+    assert (npy(mode) == np.repeat(za.argmax(2), H // A, 1)).all()    # argmax: the first maximum
+    assert (npy(bit) == zb.argmax(1)).all()
+    sel = np.sort(np.argsort(-ze, 1, kind="stable")[:, :k], 1)
+    assert (npy(eidx) == sel).all()
+    e = np.exp(np.take_along_axis(ze, sel, 1).astype(np.float64) - ze.max(1, keepdims=True))
+    gate = e / e.sum(1, keepdims=True)
+    # exp to 2 ulp and the rounded difference it takes (|z| < 8: 2^-21), k + 1 sums, a division
+    assert np.abs(npy(egate) / gate - 1).max() <= 2 * 2.0 ** -21 + (k + 6) * 2.0 ** -24
