@@ -218,11 +218,21 @@ __device__ __forceinline__ uint32_t quantize_group(const float *x, uint32_t *cod
   const _Float16 s16 = (_Float16)s32;
   const _Float16 z16 = (_Float16)mn;
   const float S = (float)s16, Z = (float)z16;
+  // The rounded quotient (x - Z) / S by one division a group and, an element,
+  // a product and one residual step: p = a R with R the rounded reciprocal is
+  // within two ulp of a / S, its residual is exact in the fma, and the corrected
+  // value lies within 2^-21 ulp of a / S before it is rounded.  A quotient of 24
+  // bits by 11 (S is an fp16 number) is no midpoint of two floats and at least
+  // 2^-12 ulp from the nearest, so it rounds as the division does.  Quotients past
+  // 2^20, infinities among them, are clamped as they are; below the normal
+  // range both round to 0; a NaN, and every element where S is 0, ends as 0.
+  const float R = S != 0.f ? __fdiv_rn(1.f, S) : 0.f;
 #pragma unroll
   for (int e = 0; e < N; ++e) {
-    float q = 0.f;
-    if (S != 0.f) q = fminf(fmaxf(rintf(__fdiv_rn(x[e] - Z, S)), 0.f), levels);
-    code[e] = uint32_t(q);
+    const float a = x[e] - Z, p = a * R;
+    const float c = fmaf(fmaf(-p, S, a), R, p);
+    const float q = fabsf(p) < 0x1p20f ? c : p;
+    code[e] = uint32_t(fminf(fmaxf(rintf(q), 0.f), levels));
   }
   return uint32_t(*(const uint16_t *)&s16) | (uint32_t(*(const uint16_t *)&z16) << 16);
 }
@@ -233,11 +243,12 @@ template <typename T, int DH, int G, int BP>
 __device__ __forceinline__ void kv_step(const CacheView &cv, int s, int bi, int g, int step,
                                         int old, int nlen, int len0, int64_t row0,
                                         const T *__restrict__ kin, const T *__restrict__ vin,
-                                        uint8_t *stage) {
+                                        bool vwave, uint8_t *stage) {
   constexpr bool Q = BP < 16;
   constexpr int EB = Q ? 1 : BP / 8;  // staged bytes per V element
+  constexpr int SR = DH * EB + 16;    // bytes per staged row: 16 more, so that rows start in
+                                      // different banks and 16-byte writes keep their alignment
   constexpr int TS = 4096 / DH, KS = DH / 32, CB = DH / 16, NG = DH / G;
-  constexpr int NIT = DH == 128 ? 2 : 1;  // 64-channel row pieces per lane
   const int lane = threadIdx.x & 63, r = lane & 31, hf = lane >> 5;
   const int Hkv = cv.Hkv;
   const int sl = step * 32 + r;
@@ -248,10 +259,9 @@ __device__ __forceinline__ void kv_step(const CacheView &cv, int s, int bi, int 
   if (live) {
     const int t = cv.pos_at(s, bi, sl) - len0;  // the token at the slot's recorded position
     const int64_t rowoff = ((row0 + t) * Hkv + g) * DH;
-#pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-      const bool isv = NIT == 2 ? it == 1 : hf == 1;
-      const int c0 = NIT == 2 ? 64 * hf : 0;
+    {
+      const bool isv = DH == 128 ? vwave : hf == 1;
+      const int c0 = DH == 128 ? 64 * hf : 0;
       const T *src = (isv ? vin : kin) + rowoff + c0;
       uint32_t code[64];
       if constexpr (Q) {
@@ -333,16 +343,22 @@ __device__ __forceinline__ void kv_step(const CacheView &cv, int s, int bi, int 
         }
       } else {
         // V codes to the wave's stage: [slot r][channel] in EB bytes
+        uint4 *d = (uint4 *)(stage + r * SR + c0 * EB);
 #pragma unroll
-        for (int e = 0; e < 64; ++e) {
-          uint8_t *d = stage + (r * DH + c0 + e) * EB;
-          if constexpr (EB == 1) *d = uint8_t(code[e]);
-          else if constexpr (EB == 2) *(uint16_t *)d = uint16_t(code[e]);
-          else *(uint32_t *)d = code[e];
+        for (int e = 0; e < 4 * EB; ++e) {
+          uint32_t v[4];
+#pragma unroll
+          for (int y = 0; y < 4; ++y) {
+            const uint32_t *c = code + (4 * e + y) * 4 / EB;
+            v[y] = EB == 1 ? c[0] | (c[1] << 8) | (c[2] << 16) | (c[3] << 24)
+                   : EB == 2 ? c[0] | (c[1] << 16) : c[0];
+          }
+          d[e] = make_uint4(v[0], v[1], v[2], v[3]);
         }
       }
     }
   }
+  if (DH == 128 && !vwave) return;  // (wave-uniform; no block barrier follows)
   __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the wave's stage writes are in
   __builtin_amdgcn_wave_barrier();
   // V: record l = lane holds channel 16 cb + l % 16 of slot
@@ -374,8 +390,9 @@ __device__ __forceinline__ void kv_step(const CacheView &cv, int s, int bi, int 
       if (slot < old) {
         keep |= mask << bt;
       } else if (slot < nlen) {
-        const uint8_t *sp = stage + (rs * DH + ch) * EB;
-        const uint32_t cv_ = EB == 1 ? *sp : EB == 2 ? *(const uint16_t *)sp : *(const uint32_t *)sp;
+        const uint8_t *sp = stage + rs * SR + ch * EB;
+        uint32_t cv_ = 0;
+        __builtin_memcpy(&cv_, __builtin_assume_aligned(sp, EB), EB);
         word |= cv_ << bt;
       }
     }
@@ -384,15 +401,21 @@ __device__ __forceinline__ void kv_step(const CacheView &cv, int s, int bi, int 
 }
 
 // One wave per (batch row b, width pool bi, kv head g, 32-slot step j of the
-// slots this append gives pool bi): lanes 0..31 take the step's slots, one
-// token each (the token at the slot's recorded position); on d_h 128 lane
-// half hf handles channels 64 hf .. 64 hf + 63 of both K and V, on d_h 64
-// half 0 does K and half 1 does V.  A lane quantizes its 64 channels of a
+// slots this append gives pool bi), on d_h 128 two, one for K and one for V:
+// lanes 0..31 take the step's slots, one token each (the token at the slot's
+// recorded position); on d_h 128 lane half hf handles channels 64 hf .. 64 hf
+// + 63 of K or V, on d_h 64 half 0 does K and half 1 does V.  A lane quantizes its 64 channels of a
 // row (one or two groups of G), stores its fp16 scale/zero pairs and its
 // slot's K words directly (every K word belongs to one slot), and stages its
 // V codes in LDS; then each lane assembles the V words of one record, which
 // hold codes of several slots, keeping the bits of slots appended before.
-// A step belongs to one wave, so no two waves write a word.
+// A step's K or V belongs to one wave, so no two waves write a word.
+// Bound by the length of a wave's own chain (16384 tokens give two waves a
+// SIMD): 1.3B, 16384 tokens 41.6 us with K and V in one wave, a division an
+// element and V codes staged byte by byte in rows of one bank, 30.4 so; 512
+// tokens 18.9 -> 13.3, 160M 18.8 -> 15.9, 410M, 333 tokens 10.0 -> 8.4 (the
+// expert lists' blocks, 14.4 -> 10.0 alone with their loads in flight
+// together, run beside it).
 template <typename T, int DH, int G>
 __global__ __launch_bounds__(256) void kv_step_kernel(CacheView cv, int B, int T_, int JS,
                                                       const int32_t *__restrict__ seq_ids,
@@ -405,9 +428,14 @@ __global__ __launch_bounds__(256) void kv_step_kernel(CacheView cv, int B, int T
     scatter_chunk(sc, blockIdx.x);
     return;
   }
-  __shared__ __align__(16) uint8_t stage_all[4][32 * DH * sizeof(T)];
+  __shared__ __align__(16) uint8_t stage_all[4][32 * (DH * sizeof(T) + 16)];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int u = __builtin_amdgcn_readfirstlane((int(blockIdx.x) - sc.nbe) * 4 + wave);
+  bool vwave = false;
+  if constexpr (DH == 128) {
+    vwave = u & 1;
+    u >>= 1;
+  }
   const int j = u % JS;
   u /= JS;
   const int g = u % cv.Hkv;
@@ -424,11 +452,12 @@ __global__ __launch_bounds__(256) void kv_step_kernel(CacheView cv, int B, int T
   uint8_t *stage = stage_all[wave];
   const int64_t row0 = int64_t(b) * T_;
   switch (bi) {
-    case 0: kv_step<T, DH, G, 2>(cv, s, bi, g, step, old, nlen, len0, row0, kin, vin, stage); break;
-    case 1: kv_step<T, DH, G, 4>(cv, s, bi, g, step, old, nlen, len0, row0, kin, vin, stage); break;
-    case 2: kv_step<T, DH, G, 8>(cv, s, bi, g, step, old, nlen, len0, row0, kin, vin, stage); break;
+    case 0: kv_step<T, DH, G, 2>(cv, s, bi, g, step, old, nlen, len0, row0, kin, vin, vwave, stage); break;
+    case 1: kv_step<T, DH, G, 4>(cv, s, bi, g, step, old, nlen, len0, row0, kin, vin, vwave, stage); break;
+    case 2: kv_step<T, DH, G, 8>(cv, s, bi, g, step, old, nlen, len0, row0, kin, vin, vwave, stage); break;
     default:
-      kv_step<T, DH, G, 8 * int(sizeof(T))>(cv, s, bi, g, step, old, nlen, len0, row0, kin, vin, stage);
+      kv_step<T, DH, G, 8 * int(sizeof(T))>(cv, s, bi, g, step, old, nlen, len0, row0, kin, vin, vwave,
+                                           stage);
       break;
   }
 }
@@ -555,7 +584,7 @@ hipError_t launch_kv_append(const triroute_cfg &cfg, const CacheView &cv, int B,
   // 32-slot steps an append can touch in one pool: all T tokens, plus the
   // partly filled step it starts in
   const int JS = (T + 31) / 32 + 1;
-  const int64_t units = int64_t(B) * 4 * cfg.n_kv_heads * JS;
+  const int64_t units = int64_t(B) * 4 * cfg.n_kv_heads * JS * (cfg.head_dim == 128 ? 2 : 1);
   const dim3 grid(unsigned((units + 3) / 4) + unsigned(job.nbe));
   const int dh = cfg.head_dim, G = cfg.kv_group;
 #define KV_STEP(TT, DH_, G_) \

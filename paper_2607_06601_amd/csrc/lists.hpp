@@ -121,10 +121,15 @@ __device__ __forceinline__ void scatter_chunk(const ScatterJob &J, int j) {
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   if (tid < E1) {
     int before = 0, all = 0;
-    for (int jj = 0; jj < nbe; ++jj) {
-      const int v = hist[jj * E1 + tid];
-      if (jj < j) before += v;
-      all += v;
+    for (int j0 = 0; j0 < nbe; j0 += 16) {  // 16 loads in flight
+      int v[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) v[i] = hist[min(j0 + i, nbe - 1) * E1 + tid];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        before += j0 + i < j ? v[i] : 0;
+        all += j0 + i < nbe ? v[i] : 0;
+      }
     }
     run[tid] = before;
     tot[tid] = all;

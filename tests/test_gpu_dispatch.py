@@ -565,3 +565,58 @@ def test_router_tail_tiles(N, d, H, E, k, groups):
     gate = e / e.sum(1, keepdims=True)
     # exp to 2 ulp and the rounded difference it takes (|z| < 8: 2^-21), k + 1 sums, a division
     assert np.abs(npy(egate) / gate - 1).max() <= 2 * 2.0 ** -21 + (k + 6) * 2.0 ** -24
+
+
+# ------------------------------------------------------- the append's quantizer
+@pytest.mark.parametrize("dh,G,act", [(64, 32, "f32"), (128, 64, "f32"), (128, 32, "bf16")])
+def test_append_codes_at_the_edges(dh, G, act):
+    """Codes of groups where the quotient sits on or next to halfway points,
+    where the fp16 scale is 0, subnormal or infinite, and where the fp16 zero
+    is infinite (but no NaN arises): the same bytes as the oracle's division."""
+    c, T, Hkv = tr.make_cfg(256, 2, 1, dh, 64, 4, 1, 128, G, act), 96, 1
+    rng = gen.stream(91, "edges", dh, G)
+    x = np.empty((2, T, Hkv, dh // G, G), np.float32)
+    for i in range(2):
+        for t in range(T):
+            bits = (2, 4, 8)[t % 3]
+            lv, u = 2 ** bits - 1, rng.random((Hkv, dh // G, G))
+            scale = np.float16(2.0 ** rng.integers(-24, 10) * (1 + rng.integers(0, 1024) / 1024))
+            kind = t // 3 % 8
+            half = (rng.integers(0, lv, u.shape) + 0.5) * np.float64(scale)
+            g = half * (1 + rng.choice([0, 6e-8, -6e-8, 2e-7, -2e-7], u.shape))
+            g[..., 0], g[..., 1] = 0, lv * np.float64(scale)
+            if kind == 1:
+                g = g + np.float64(scale) * rng.integers(-8, 8)   # zero not 0
+            elif kind == 2:
+                g = np.full(u.shape, 0.3)                         # scale 0
+            elif kind == 3:
+                g = u * lv * 1.5e-7                               # subnormal scale
+            elif kind == 4:
+                g = u * 1e-9                                      # scale rounds to 0
+            elif kind == 5:
+                g = u * 3e37                                      # infinite scale
+                g[..., 0] = 0
+            elif kind == 6:
+                g = u * lv - 1e5                                  # zero -inf
+            elif kind == 7:
+                g = u * lv + 1e5                                  # zero +inf
+            x[i, t] = g
+    x = gen.to_act(x.reshape(2, T, Hkv, dh), act)
+    bit = (np.arange(T) % 3).astype(np.uint8)
+    cache = tr.KVCache(c, 1, 128)
+    _append(c, cache, 0, x[0], x[1], bit, act)
+    for bi, nb in enumerate((2, 4, 8)):
+        n = int((bit == bi).sum())
+        ko = torch.zeros(n, Hkv, dh, dtype=torch.uint8, device=DEV)
+        vo = torch.zeros_like(ko)
+        ks = torch.zeros(n, Hkv, dh // G, 2, dtype=torch.int16, device=DEV)
+        vs = torch.zeros_like(ks)
+        tr.kv_export(c, cache, 0, bi, 0, n, ko, vo, ks, vs,
+                     torch.zeros(n, dtype=torch.int32, device=DEV))
+        torch.cuda.synchronize()
+        for src, out, sz in ((x[0], ko, ks), (x[1], vo, vs)):
+            with np.errstate(over="ignore"):
+                codes, s16, z16 = oracle.quant.quantize(src[bit == bi], nb, G)
+            np.testing.assert_array_equal(npy(out), codes)
+            np.testing.assert_array_equal(npy(sz)[..., 0], s16.view(np.int16))
+            np.testing.assert_array_equal(npy(sz)[..., 1], z16.view(np.int16))
