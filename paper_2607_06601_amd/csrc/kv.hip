@@ -412,7 +412,7 @@ __device__ __forceinline__ void kv_step(const CacheView &cv, int s, int bi, int 
 // A step's K or V belongs to one wave, so no two waves write a word.
 // Bound by the length of a wave's own chain (16384 tokens give two waves a
 // SIMD): 1.3B, 16384 tokens 41.6 us with K and V in one wave, a division an
-// element and V codes staged byte by byte in rows of one bank, 30.4 so; 512
+// element and V codes staged byte by byte in rows of one bank, 30.4 so; 2000
 // tokens 18.9 -> 13.3, 160M 18.8 -> 15.9, 410M, 333 tokens 10.0 -> 8.4 (the
 // expert lists' blocks, 14.4 -> 10.0 alone with their loads in flight
 // together, run beside it).

@@ -4,8 +4,8 @@
 // in a few blocks, and a launch of its own for each would leave the chip idle
 // for its length: of these 2.5 to 5 us each, 16 at 16384 tokens).  A layer
 // measured with the launches of its own and with the shared ones: 160M decode
-// of one row 70.9 -> 67.6 us, 410M decode of 32 rows 130 -> 127.7, 410M prefill
-// of 333 tokens 163.5 -> 152.2, a 1.3B prefill chunk of 512 736 -> 727.
+// of one row 70.9 -> 67.6 us, 410M decode of 64 rows 130 -> 127.7, 410M prefill
+// of 333 tokens 163.5 -> 152.2, a 1.3B prefill chunk of 2000 736 -> 727.
 #pragma once
 
 #include "kernels.hpp"

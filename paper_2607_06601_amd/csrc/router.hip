@@ -182,8 +182,8 @@ __global__ __launch_bounds__(256) void trunk1_kernel(const T *__restrict__ x,
 // tokens the trunk's chunks are summed by 8 / TB groups of threads, a run of
 // chunks each, whose sums are added in order.
 // (Weights staged in LDS by blocks of eight waves, a CU each: 20.7 us at 333
-// tokens, 24 at 512 of the 1.3B layer, 38 at 16384; so: 10, 12.9, 25.4.  A
-// prefill of 333 tokens at 410M 152 -> 139 us, of 512 at 1.3B 727 -> 700.)
+// tokens, 24 at 2000 of the 1.3B layer, 38 at 16384; so: 10, 12.9, 25.4.  A
+// prefill of 333 tokens at 410M 152 -> 139 us, of 2000 after 7000 at 1.3B 727 -> 708.)
 constexpr int RT_TB = 16, RT_DR = 128, RT_NZ = 112, RT_TILES = 256;
 constexpr int RT_LD = RT_DR + 4, RT_ZLD = RT_NZ + 4;
 
@@ -578,7 +578,7 @@ hipError_t launch_router(const triroute_cfg &cfg, int N, const void *x, const fl
   }
   if (N <= 256 && ks <= RTB_MAXKS) {  // a CU a token, where the vector units are the shorter way:
     // the same layers with the tiles of one token instead, 160M decode of one
-    // row 68.0 -> 68.8 us, 410M of 32 rows 128.0 -> 128.6, fp32 of 17 83.4 -> 84.6
+    // row 68.0 -> 68.8 us, 410M of 64 rows 128.0 -> 128.6, fp32 of 128 83.4 -> 84.6
     router_tail_blk_kernel<<<dim3(N), 256, 0, st>>>(
         u, ks, w.b1, w.W2, w.b2, w.gr, w.Wa, w.ca, w.We, w.ce, w.Wb, w.cb, mode, bit, eidx, egate,
         N, cfg.n_heads, attn_groups(cfg), cfg.n_experts + 1, cfg.top_k, cfg.rms_eps, tap);
