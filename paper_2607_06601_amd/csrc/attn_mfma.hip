@@ -1656,10 +1656,12 @@ __global__ __launch_bounds__(64 * PF_WAVES) __attribute__((amdgpu_waves_per_eu(2
   const int base = cv.seq_len[s] - a.T;
   // union of the quartet's key ranges (block-uniform: every wave computes it)
   int lo_u = INT_MAX, hi_u = -1;
+  bool any = false;  // the block has a query
   for (int k = 0; k < PF_WAVES * PF_HEADS && quart * PF_WAVES * PF_HEADS + k < a.R; ++k) {
     const int sg = (b * a.H + g * a.R + quart * PF_WAVES * PF_HEADS + k) * 2 + (m - 1);
     const int ck = a.cnt[sg];
     if (qt * 16 >= ck) continue;
+    any = true;
     const int32_t *lk = a.idx + int64_t(sg) * a.T;
     const int pmin = base + lk[qt * 16], pmax = base + lk[min(qt * 16 + 15, ck - 1)];
     lo_u = min(lo_u, m == TRIROUTE_LOCAL ? pmin - a.w + 1 : 0);
@@ -1684,16 +1686,20 @@ __global__ __launch_bounds__(64 * PF_WAVES) __attribute__((amdgpu_waves_per_eu(2
     const bool valid = act[hq] && j < count[hq];
     const int t = valid ? lst[j] : 0;
     const int P = base + t;
+    // (the tokens of a row dropped for its length may lie before position 0:
+    // such a query has no key)
+    const bool keys = valid && P >= 0;
     load_q<DH, G>(a.q + (int64_t(b * a.T + t) * a.H + h) * DH, valid, qop[hq], qsum[hq]);
-    cm[hq].lo = valid ? (m == TRIROUTE_LOCAL ? P - a.w + 1 : 0) : 1;
-    cm[hq].hi = valid ? P : 0;
-    mlo[hq] = valid ? uint32_t(cm[hq].lo) : 0xFFFFFFFFu;
-    mspan[hq] = valid ? uint32_t(cm[hq].hi - cm[hq].lo) : 0u;
+    cm[hq].lo = keys ? (m == TRIROUTE_LOCAL ? P - a.w + 1 : 0) : 1;
+    cm[hq].hi = keys ? P : 0;
+    mlo[hq] = keys ? uint32_t(cm[hq].lo) : 0xFFFFFFFFu;
+    mspan[hq] = keys ? uint32_t(cm[hq].hi - cm[hq].lo) : 0u;
   }
   lo_u = __builtin_amdgcn_readfirstlane(lo_u);
   hi_u = __builtin_amdgcn_readfirstlane(hi_u);
-  if (hi_u < 0) return;
-  // tile ranges of the union in every pool
+  if (!any) return;
+  // tile ranges of the union in every pool (none where all its queries lie
+  // before position 0: they still write their zeros or empty partials)
   int len[4], key[8], res[8];
 #pragma unroll
   for (int bi = 0; bi < 4; ++bi) {

@@ -128,6 +128,59 @@ def test_prefill_split_key_ranges(monkeypatch, B, T, H, Hkv, dh, w, ctx, pages):
         assert not npy(t["o"]).reshape(B, -1)[1].any()
 
 
+@pytest.mark.parametrize("act,T,len0,layer", [
+    ("bf16", 1500, 700, True),      # key ranges split: 800 queries before the first key
+    ("bf16", 40, 37, True),         # unsplit; a query tile on both sides of position 0
+    ("bf16", 1500, 700, False), ("f32", 300, 70, True), ("f32", 300, 70, False),
+])
+def test_prefill_of_a_dropped_row(monkeypatch, act, T, len0, layer):
+    """A row dropped for its length (len0 + T tokens past the capacity) whose
+    first queries would lie before the sequence's first position: they have no
+    key, so their attention is zero (not what the scratch or o held); the other
+    queries of the row see the keys that are there, and the row beside it is
+    as without it."""
+    H, Hkv, dh, w = 4, 2, 64, 400
+    L = _small_layer(monkeypatch, B=2, T=T, H=H, Hkv=Hkv, dh=dh, w=w, act=act)
+    D = DeviceLayer(L)
+    c, N = D.cfg, 2 * T
+    rng = gen.stream(43, "dropped", T, len0)
+    kv = gen.kv_block(43, len0, Hkv, dh, act, 0.8)
+    bits = rng.integers(0, 4, len0).astype(np.uint8)
+    out = []
+    for dropped in (True, False):
+        cache = tr.KVCache(c, 2, T + len0 - dropped)
+        _append(c, cache, 0, *kv, bits, act)
+        t = {n: torch.full((N, m), float("nan"), dtype=D.act, device=DEV)
+             for n, m in (("q", H * dh), ("o", H * dh), ("xt", 256))}
+        t["mode"] = torch.full((N, H), 9, dtype=torch.uint8, device=DEV)
+        x_out = torch.full((N, 256), float("nan"), dtype=D.act, device=DEV)
+        ws = tr.workspace(c, tr.OP_LAYER_PREFILL, 2, T)
+        ws.fill_(0xFF)                           # scratch holds NaNs
+        print(f"dropped row act={act} T={T} len0={len0} layer={layer} {dropped}", flush=True)
+        tr.layer_prefill(c, 2, T, D.x, D.psi, D.rw, D.dw, D.mw, cache, x_out, ws,
+                         taps=tr.Taps(**{n: v.data_ptr() for n, v in t.items()}))
+        assert cache.status() == (tr.CACHE_OVERFLOW if dropped else 0)
+        if not layer:
+            cmp = tr.CompactionBuffers(c, 2, T)
+            cc = oracle.compact(npy(t["mode"]), np.zeros((N, 1), np.int32), 2, T, H, 4, 1)
+            cmp.attn_cnt.copy_(torch.from_numpy(cc["attn_cnt"]))
+            cmp.attn_idx.copy_(torch.from_numpy(np.maximum(cc["attn_idx"], 0).reshape(-1)))
+            t["o"].fill_(float("nan"))
+            tr.attn_prefill(c, 2, T, t["q"], cache, t["mode"], cmp.struct, t["o"])
+        torch.cuda.synchronize()
+        out.append(dict({n: npy(v).reshape(2, T, -1) for n, v in t.items()}, x_out=npy(x_out)))
+    got, whole = out
+    neg = T - len0                               # queries at positions < 0
+    assert not got["o"][0, :neg].any()
+    pos = np.arange(neg, T) - neg
+    khat, vhat, _ = oracle.layer.store_kv(*kv, bits, dict(G=64))
+    ref = oracle.attention_seq(got["q"][0, neg:].reshape(-1, H, dh).astype(np.float64), pos, khat,
+                               vhat, got["mode"][0, neg:], w)
+    assert_close(got["o"][0, neg:], ref.reshape(len(pos), -1), act, "o of the dropped row")
+    np.testing.assert_array_equal(got["o"][1], whole["o"][1])
+    assert np.isfinite(got["x_out"]).all()
+
+
 # ------------------------------------------------------- GEMM tile choices
 @pytest.mark.parametrize("H,Hkv,dh,d,n_tok", [
     (4, 1, 64, 128, 1), (3, 1, 64, 128, 33),           # O-projection: two K groups (K 192: one)
