@@ -828,12 +828,13 @@ int triroute_router_relaxed_backward(const triroute_cfg *cfg, int B, int T, cons
   tap.z = xw.z;
   tap.a1 = bw.a1;
   tap.hpre = bw.hpre;
+  tap.xlast = bw.da1;  // read there, then overwritten by da1
   // (its n1 is not wanted)
   CHECK_HIP(tr::launch_router(*cfg, N, x, psi, wf, nullptr, bw.mode, bw.bit, bw.eidx, bw.egate,
                               rw.rinv, rw.u, nullptr, st, tap),
             "router launch");
   tr::RelaxBwdJob j;
-  j.z = xw.z; j.hh = xw.h; j.a1 = bw.a1; j.hpre = bw.hpre;
+  j.z = xw.z; j.hh = xw.h; j.a1 = bw.a1; j.hpre = bw.hpre; j.upart = rw.u;
   j.y_attn = fwd->y_attn; j.y_bits = fwd->y_bits; j.egate = egate; j.eidx = eidx; j.pos = p->pos;
   j.g_attn = gin->g_attn; j.g_bits = gin->g_bits; j.g_gate = gin->g_gate;
   j.stats = fwd->stats; j.usage = fwd->usage_exp; j.lambda = gin->lambda;

@@ -44,9 +44,11 @@ __device__ __forceinline__ float2 rope_entry(const RopeJob &r, int row, int j) {
 }
 // Optional copies of the controller tail's intermediates (any may be NULL):
 // h^ [N, 128], the head logits z [N, 3 A + E + 5], the trunk's pre-GELU
-// a1 = W1 [n1; psi] + b1 [N, 128] and h = W2 u + b2 before its norm [N, 128].
+// a1 = W1 [n1; psi] + b1 [N, 128], h = W2 u + b2 before its norm [N, 128], and,
+// where a K chunk of the trunk holds inputs of x and psi, that chunk's partial
+// products over the inputs of x [N, 128].
 struct TailTap {
-  float *h = nullptr, *z = nullptr, *a1 = nullptr, *hpre = nullptr;
+  float *h = nullptr, *z = nullptr, *a1 = nullptr, *hpre = nullptr, *xlast = nullptr;
 };
 // rope (optional): the first RMSNorm also writes that rotation table
 hipError_t launch_router(const triroute_cfg &cfg, int N, const void *x, const float *psi,
@@ -189,6 +191,7 @@ struct RelaxGradOut {
 };
 struct RelaxBwdJob {
   const float *z, *hh, *a1, *hpre;  // taps of the recomputed trunk and tail
+  const float *upart;  // the recomputed trunk's partial products (router_split's chunks)
   const float *y_attn, *y_bits, *egate;
   const int32_t *eidx, *pos;
   const float *g_attn, *g_bits, *g_gate;
@@ -198,6 +201,7 @@ struct RelaxBwdJob {
   float tau_a, tau_b, zeta, alpha, beta, gamma;
   // scratch
   const float *rinv;  // the first norm's row scales (the recomputed router's)
+  // da1 holds the xlast tap on entry
   float *dz, *dh, *da1, *u, *tgr, *lmsq, *cx, *part, *G, *dc;
   double *lmsq_sum;
   RelaxGradOut out;

@@ -44,10 +44,12 @@ struct BwdTokArgs {
   const double *stats, *usage;  // the forward's batch statistics
   const double *rho;            // [3] or NULL (1)
   const double *lambda;         // [2] or NULL (0)
-  const float *rinv, *psi, *W1, *b1;
+  const float *rinv;
+  const float *upart, *xlast;   // the trunk's products with x: nx whole chunks, and xlast's
+  int nx;
   float *dz, *dh, *da1, *u, *tgr, *lmsq;  // dz: [N][DR], zero past the logits
   float *cx;                    // [N]: factor of x in dx
-  int N, H, A, E1, k, dh_, w, dkv, d, dpsi;
+  int N, H, A, E1, k, dh_, w, dkv, d;
   float inv_ta, inv_tb, zeta, alpha, beta, gamma, eps, kappa_e;
 };
 
@@ -251,29 +253,29 @@ __global__ __launch_bounds__(256) void relax_bwd_tok_kernel(BwdTokArgs p) {
   *(float4 *)dzw[lane] = make_float4(dh[0][0], dh[1][0], dh[2][0], dh[3][0]);
   *(float4 *)dzw[lane + 64] = make_float4(dh[0][1], dh[1][1], dh[2][1], dh[3][1]);
   __builtin_amdgcn_wave_barrier();
-  // ---- h = W2 u + b2: du = W2^T dh; u = GELU(a1)
-  product(p.W2, DR, g);
-  // sum_j dn1_j n1_j = sum_c da1_c (W1 n1)_c, and W1 n1 = a1 - b1 - W1_psi psi
+  // sum_j dn1_j n1_j = sum_c da1_c (W1 n1)_c.  W1 n1 comes from the trunk's
+  // partial products with x: as a1 - b1 - W1_psi psi it would lose its low bits
+  // to a large bias or side feature (1000 times W1 n1, d 64: elements of dx were
+  // off by up to 3e-4 of themselves).  Loaded ahead of the product, whose time
+  // covers it (703 us the 1.3B training step of 16384 tokens, 710 behind it).
   float x[TOKS][2], y[TOKS][2];
 #pragma unroll
   for (int q = 0; q < TOKS; ++q) {
     const int64_t at = int64_t(min(t0 + q, p.N - 1)) * DR + lane;
     x[q][0] = p.a1[at];
     x[q][1] = p.a1[at + 64];
-    y[q][0] = x[q][0] - p.b1[lane];
-    y[q][1] = x[q][1] - p.b1[lane + 64];
+    y[q][0] = p.xlast ? p.xlast[at] : 0.f;  // (an entry of da1's own: read before it is written)
+    y[q][1] = p.xlast ? p.xlast[at + 64] : 0.f;
   }
-  const float *w0 = p.W1 + int64_t(lane) * (p.d + p.dpsi) + p.d;
-  const float *w1 = w0 + int64_t(64) * (p.d + p.dpsi);
-  for (int j = 0; j < p.dpsi; ++j) {
-    const float wj0 = w0[j], wj1 = w1[j];
+  for (int s = 0; s < p.nx; ++s)
 #pragma unroll
     for (int q = 0; q < TOKS; ++q) {
-      const float ps = p.psi[int64_t(min(t0 + q, p.N - 1)) * p.dpsi + j];
-      y[q][0] = fmaf(-wj0, ps, y[q][0]);
-      y[q][1] = fmaf(-wj1, ps, y[q][1]);
+      const int64_t at = (int64_t(s) * p.N + min(t0 + q, p.N - 1)) * DR + lane;
+      y[q][0] += p.upart[at];
+      y[q][1] += p.upart[at + 64];
     }
-  }
+  // ---- h = W2 u + b2: du = W2^T dh; u = GELU(a1)
+  product(p.W2, DR, g);
 #pragma unroll
   for (int q = 0; q < TOKS; ++q) {
     const float d0 = g[q][0] * gelu_grad_f(x[q][0]), d1 = g[q][1] * gelu_grad_f(x[q][1]);
@@ -708,10 +710,17 @@ hipError_t launch_relax_backward(const triroute_cfg &cfg, int N, const void *x, 
   p.g_ya = j.g_attn; p.g_yb = j.g_bits; p.g_gate = j.g_gate;
   p.W2 = w.W2; p.gr = w.gr; p.stats = j.stats; p.usage = j.usage; p.rho = j.rho_io;
   p.lambda = j.lambda;
-  p.rinv = j.rinv; p.psi = psi; p.W1 = w.W1; p.b1 = w.b1;
+  p.rinv = j.rinv;
+  {
+    int ks, kchunk;
+    router_split(N, K1, ks, kchunk);
+    p.nx = dpsi > 0 ? d / kchunk : ks;
+    p.upart = j.upart;
+    p.xlast = dpsi > 0 && d % kchunk != 0 ? j.da1 : nullptr;
+  }
   p.dz = j.dz; p.dh = j.dh; p.da1 = j.da1; p.u = j.u; p.tgr = j.tgr; p.lmsq = j.lmsq; p.cx = j.cx;
   p.N = N; p.H = cfg.n_heads; p.A = A; p.E1 = E1; p.k = cfg.top_k; p.dh_ = cfg.head_dim;
-  p.w = cfg.window; p.dkv = cfg.n_kv_heads * cfg.head_dim; p.d = d; p.dpsi = dpsi;
+  p.w = cfg.window; p.dkv = cfg.n_kv_heads * cfg.head_dim; p.d = d;
   p.inv_ta = 1.f / j.tau_a; p.inv_tb = 1.f / j.tau_b; p.zeta = j.zeta; p.alpha = j.alpha;
   p.beta = j.beta; p.gamma = j.gamma; p.eps = cfg.rms_eps;
   p.kappa_e = 3.f * float(cfg.d_model) * float(cfg.d_ff);

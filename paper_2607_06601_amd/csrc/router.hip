@@ -71,14 +71,17 @@ void router_split(int N, int K, int &ks, int &kchunk) {
 // block's K chunk, with n1 = x r g1 formed on load (fp32 MFMA 16x16x4).
 // Block: 64 rows x 128 outputs, 4 waves of 16 rows; the next K step is
 // fetched into registers while the current one is multiplied from LDS.
-template <typename T>
+// XL: where the chunk holds inputs of x and of psi, the products with x alone
+// go to xlast (the backward pass wants W1 n1 without the other terms of a1).
+template <typename T, bool XL>
 __global__ __launch_bounds__(256) void trunk1_kernel(const T *__restrict__ x,
                                                      const float *__restrict__ rinv,
                                                      const float *__restrict__ g1,
                                                      const float *__restrict__ psi,
                                                      const float *__restrict__ W1,
                                                      float *__restrict__ upart, int N, int d,
-                                                     int dpsi, int kchunk) {
+                                                     int dpsi, int kchunk,
+                                                     float *__restrict__ xlast) {
   constexpr int BM = 64, BK = 32, LD = BK + 1;
   __shared__ float As[2][BM][LD];
   __shared__ float Bs[2][128][LD];
@@ -141,7 +144,18 @@ __global__ __launch_bounds__(256) void trunk1_kernel(const T *__restrict__ x,
   put(0);
   __syncthreads();
   int buf = 0;
+  // accumulator r of the lane: row 16 wave + 4 (lane / 16) + r, columns 16 j + lane % 16
+  auto store = [&](float *out) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = m0 + 16 * wave + 4 * (lane >> 4) + r;
+      if (row >= N) continue;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) out[int64_t(row) * 128 + 16 * j + (lane & 15)] = acc[j][r];
+    }
+  };
   for (int k0 = kb; k0 < ke; k0 += BK) {
+    if (XL && k0 == d && kb < d) store(xlast);  // (d and the chunks are multiples of BK)
     const bool more = k0 + BK < ke;
     if (more) fetch(k0 + BK);
 #pragma unroll
@@ -156,14 +170,7 @@ __global__ __launch_bounds__(256) void trunk1_kernel(const T *__restrict__ x,
     __syncthreads();
     buf ^= 1;
   }
-  float *out = upart + int64_t(blockIdx.y) * N * 128;
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int row = m0 + 16 * wave + 4 * (lane >> 4) + r;
-    if (row >= N) continue;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) out[int64_t(row) * 128 + 16 * j + (lane & 15)] = acc[j][r];
-  }
+  store(upart + int64_t(blockIdx.y) * N * 128);
 }
 
 // Tail, a tile of TB <= 16 tokens a block of four waves:
@@ -568,13 +575,13 @@ hipError_t launch_router(const triroute_cfg &cfg, int N, const void *x, const fl
   if (cfg.act == TRIROUTE_BF16) {
     rms_norm1_kernel<bf16><<<g1, 256, 0, st>>>((const bf16 *)x, w.g1, rinv, (bf16 *)n1, N, d,
                                                cfg.rms_eps, rj);
-    trunk1_kernel<bf16><<<g2, 256, 0, st>>>((const bf16 *)x, rinv, w.g1, psi, w.W1, u, N, d,
-                                            cfg.d_psi, kchunk);
+    (tap.xlast ? trunk1_kernel<bf16, true> : trunk1_kernel<bf16, false>)<<<g2, 256, 0, st>>>(
+        (const bf16 *)x, rinv, w.g1, psi, w.W1, u, N, d, cfg.d_psi, kchunk, tap.xlast);
   } else {
     rms_norm1_kernel<float><<<g1, 256, 0, st>>>((const float *)x, w.g1, rinv, (float *)n1, N, d,
                                                 cfg.rms_eps, rj);
-    trunk1_kernel<float><<<g2, 256, 0, st>>>((const float *)x, rinv, w.g1, psi, w.W1, u, N, d,
-                                             cfg.d_psi, kchunk);
+    (tap.xlast ? trunk1_kernel<float, true> : trunk1_kernel<float, false>)<<<g2, 256, 0, st>>>(
+        (const float *)x, rinv, w.g1, psi, w.W1, u, N, d, cfg.d_psi, kchunk, tap.xlast);
   }
   if (N <= 256 && ks <= RTB_MAXKS) {  // a CU a token, where the vector units are the shorter way:
     // the same layers with the tiles of one token instead, 160M decode of one

@@ -411,17 +411,22 @@ def test_f32_attention(H, Hkv, dh, G, w, lens):
 
 
 # --------------------------------------------------- controller's backward
-@pytest.mark.parametrize("B,T,d,dpsi,H,E,k,groups,act", [
-    (1, 1, 64, 0, 2, 1, 1, 0, "bf16"),          # one token, one column tile, no side features
-    (1, 31, 128, 4, 4, 3, 2, 2, "f32"),         # fewer tokens than a tile
-    (2, 67, 192, 32, 4, 2, 3, 1, "bf16"),       # a ragged wave of tokens, the most side features
-    (1, 129, 2048, 8, 16, 16, 2, 0, "bf16"),    # one token past a block, many column tiles
-    (3, 683, 64, 8, 30, 12, 2, 0, "f32"),       # 107 logits; several chunks, few column tiles
+@pytest.mark.parametrize("B,T,d,dpsi,H,E,k,groups,act,big", [
+    (1, 1, 64, 0, 2, 1, 1, 0, "bf16", 0),       # one token, one column tile, no side features
+    (1, 31, 128, 4, 4, 3, 2, 2, "f32", 0),      # fewer tokens than a tile
+    (2, 67, 192, 32, 4, 2, 3, 1, "bf16", 0),    # a ragged wave of tokens, the most side features
+    (1, 129, 2048, 8, 16, 16, 2, 0, "bf16", 0), # one token past a block, many column tiles
+    (3, 683, 64, 8, 30, 12, 2, 0, "f32", 0),    # 107 logits; several chunks, few column tiles
+    (1, 300, 64, 8, 4, 3, 2, 0, "f32", 1000),   # biases and side features far above W1 n1:
+    (1, 33, 64, 0, 4, 3, 2, 0, "bf16", 1000),   # psi in a chunk of K of its own; no psi;
+    (1, 9000, 320, 32, 4, 3, 2, 0, "f32", 1000),  # three chunks of x and one of both
 ])
-def test_relaxed_backward_tiles(B, T, d, dpsi, H, E, k, groups, act):
+def test_relaxed_backward_tiles(B, T, d, dpsi, H, E, k, groups, act, big):
     """Gradients of the relaxed controller against fp64 torch autograd at the
     edges of the token, column and chunk tiles, within the fp32 bound (the
-    sums run over at most 2049 tokens)."""
+    sums run over at most 9000 tokens).  big: trunk biases and side features of
+    that size, whose share of a1 is not to cost dx the bits of W1 n1 (they
+    saturate the GELU, so that the rounding of a1 itself moves nothing)."""
     A, N, dev = groups or H, B * T, dict(device=DEV)
     c = tr.make_cfg(d, H, 2, 64, 64, E, k, 128, 64, act, d_psi=dpsi, attn_groups=groups)
     g = torch.Generator(**dev)
@@ -434,8 +439,11 @@ def test_relaxed_backward_tiles(B, T, d, dpsi, H, E, k, groups, act):
              W2=rnd(128, 128, std=0.1), b2=rnd(128, std=0.02), gr=1 + rnd(128, std=0.02),
              Wa=rnd(3 * A, 128, std=0.1), ca=rnd(3 * A, std=0.1), We=rnd(E + 1, 128, std=0.1),
              ce=rnd(E + 1, std=0.1), Wb=rnd(4, 128, std=0.1), cb=rnd(4, std=0.1))
+    if big:
+        w["b1"] = big * (2 + torch.rand(128, generator=g, **dev)) * rnd(128).sign()
     rw = tr.RouterW(*(t.data_ptr() for t in w.values()))
     x, psi = rnd(N, d).to(torch_act(act)), rnd(N, max(dpsi, 1))[:, :dpsi].contiguous()
+    psi *= big or 1
     pos = torch.arange(N, dtype=torch.int32, **dev)
     ga, gb = rnd(N, A, 3), rnd(N, 4)
     p = tr.RelaxParams(g_attn=ga.data_ptr(), g_bits=gb.data_ptr(), pos=pos.data_ptr(), tau_a=1.3,
