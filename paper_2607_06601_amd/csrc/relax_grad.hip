@@ -657,13 +657,15 @@ __global__ __launch_bounds__(256) void heads_final_kernel(const float *__restric
   }
 }
 
-// Chunks of the gram launches: enough blocks for two a CU, at least 32 tokens
-// and at most GR_CHUNK of them in an fp32 partial.
-constexpr int GR_BLOCKS = 1024, GR_CHUNK = 544;
-int gram_chunk(int tiles, int N) {
+// Chunks of the gram launches: about GR_BLOCKS blocks (four a CU), at least 32
+// tokens and at most `most` of them in an fp32 partial sum: 512 for the
+// trunk's gram, 128 for the heads' (and dW2's, in their launch), beyond which
+// the partials' rounding shows in the result.
+constexpr int GR_BLOCKS = 1024, GR_MOST_X = 512, GR_MOST = 128;
+int gram_chunk(int tiles, int N, int most) {
   const int want = std::max(1, GR_BLOCKS / tiles);
   const int c = ((N + want - 1) / want + GR_KT - 1) / GR_KT * GR_KT;
-  return std::min(c, GR_CHUNK);
+  return std::min(c, most);
 }
 int chunks_of(int N, int chunk) { return (N + chunk - 1) / chunk; }
 
@@ -677,8 +679,8 @@ PartLayout part_layout(const triroute_cfg &c, int N) {
   PartLayout L;
   const size_t K1 = size_t(c.d_model + c.d_psi);
   L.x_tiles = c.d_model / 64;
-  L.x_chunk = gram_chunk(L.x_tiles, N);
-  L.s_chunk = gram_chunk(5, N);
+  L.x_chunk = gram_chunk(L.x_tiles, N, GR_MOST_X);
+  L.s_chunk = gram_chunk(5, N, GR_MOST);
   L.nx = chunks_of(N, L.x_chunk);
   L.ns = chunks_of(N, L.s_chunk);
   L.ncs = chunks_of(N, CS_CHUNK);

@@ -496,6 +496,64 @@ def test_relaxed_backward_tiles(B, T, d, dpsi, H, E, k, groups, act, big):
             assert_close(npy(t), npy(v[n[1:]].grad), "f32", n)
 
 
+def test_relaxed_backward_partial_sums():
+    """120000 equal tokens: a head's weight gradient is the outer product of
+    its bias gradient (their sum of dz, added in fp64) and the mean of h^.  Equal
+    terms round alike, so the fp32 partial sums show their length: of n terms p
+    the k-th addition errs by half an ulp of k p at most, 2^-24 k p, together
+    2^-24 n / 2 of the sum; n is 128 tokens.  (fp64 adds the partial sums.)"""
+    N, H, E, k, d, A, dev = 120000, 4, 3, 2, 64, 4, dict(device=DEV)
+    c = tr.make_cfg(d, H, 2, 64, 64, E, k, 128, 64, "f32", attn_groups=0)
+    g = torch.Generator(**dev)
+    g.manual_seed(73)
+
+    def rnd(*shape, std=1.0):
+        return torch.randn(shape, generator=g, **dev) * std
+
+    def same(*shape):
+        return rnd(1, *shape).expand(N, *shape).contiguous()
+
+    w = dict(g1=1 + rnd(d, std=0.02), W1=rnd(128, d + 8, std=0.05), b1=rnd(128, std=0.02),
+             W2=rnd(128, 128, std=0.1), b2=rnd(128, std=0.02), gr=1 + rnd(128, std=0.02),
+             Wa=rnd(3 * A, 128, std=0.1), ca=rnd(3 * A, std=0.1), We=rnd(E + 1, 128, std=0.1),
+             ce=rnd(E + 1, std=0.1), Wb=rnd(4, 128, std=0.1), cb=rnd(4, std=0.1))
+    rw = tr.RouterW(*(t.data_ptr() for t in w.values()))
+    x, psi, ga, gb = same(d), same(8), same(A, 3), same(4)
+    pos = torch.zeros(N, dtype=torch.int32, **dev)
+    p = tr.RelaxParams(g_attn=ga.data_ptr(), g_bits=gb.data_ptr(), pos=pos.data_ptr(), tau_a=1.3,
+                       tau_b=0.8)
+    f64 = dict(dtype=torch.float64, **dev)
+    o = dict(y_attn=torch.empty(N, A, 3, **dev), y_bits=torch.empty(N, 4, **dev),
+             c_flops=torch.empty(N, **dev), c_mem=torch.empty(N, **dev),
+             stats=torch.empty(tr.RELAX_NSTAT, **f64), usage_exp=torch.empty(2, E + 1, **f64),
+             h_mean=torch.empty(128, **dev), h_var=torch.empty(128, **dev))
+    fwd = tr.RelaxOut(**{n: v.data_ptr() for n, v in o.items()})
+    eidx, egate = torch.empty(N, k, dtype=torch.int32, **dev), torch.empty(N, k, **dev)
+    print(f"partial sums N={N}", flush=True)
+    tr.router_relaxed(c, 1, N, x, psi, rw, p, torch.empty_like(x),
+                      torch.empty(N, H, dtype=torch.uint8, **dev),
+                      torch.empty(N, dtype=torch.uint8, **dev), eidx, egate,
+                      tr.CompactionBuffers(c, 1, N).struct, fwd,
+                      tr.workspace(c, tr.OP_ROUTER_RELAXED, 1, N))
+    ua, ub, ue = same(A, 3), same(4), same(k)
+    gin = tr.RelaxGradIn(g_attn=ua.data_ptr(), g_bits=ub.data_ptr(), g_gate=ue.data_ptr(), rho_m=0.0)
+    out = {"d" + n: torch.empty_like(v) for n, v in w.items()}
+    out.update(dx=torch.empty(N, d, **dev), dpsi=torch.empty(N, 8, **dev))
+    tr.router_relaxed_backward(c, 1, N, x, psi, rw, p, fwd, eidx, egate, gin,
+                               tr.RelaxGradOut(**{n: v.data_ptr() for n, v in out.items()}),
+                               tr.workspace(c, tr.OP_ROUTER_RELAXED_BACKWARD, 1, N))
+    torch.cuda.synchronize()
+    h = npy(o["h_mean"]).astype(np.float64)
+    for n in "aeb":
+        ref = np.outer(npy(out["dc" + n]).astype(np.float64), h)
+        on = np.abs(ref) > 0                     # (options outside the top k: zeros)
+        assert on.mean() >= k / (E + 1) and not npy(out["dW" + n])[~on].any(), n
+        err = np.abs(npy(out["dW" + n])[on] / ref[on] - 1).max() / 2.0 ** -24
+        # the bias gradient, the mean and the result are each rounded once more
+        note(f"dW{n} (bound 67 units of 2^-24)", err / 67)
+        assert err <= 67, (n, err)
+
+
 # ------------------------------------------- lists and slots beside other work
 @pytest.mark.parametrize("B,T,prefill", [
     (1, 1, False), (512, 1, False), (513, 1, False),   # decode: one chunk of 1024 assignments, two
