@@ -1173,8 +1173,11 @@ struct PrefillArgs {
   bf16 *o;
   float *part;  // [B*T*H][NS]: rows of a split mode, m, l (stride 2), then O (stride DH)
   int B, T, H, Hkv, R, NQ, w, QT;  // NQ = head quartets per kv head, QT = ceil(T / 16)
-  int NS, nsf, nsl;  // partials per row; chunks of a full-mode and of a local-mode block
+  int NS, nsf, nsl;  // partials per row; most chunks of a full-mode and of a local-mode block
   float scale2;
+  // chunks of a sequence of `len` tokens (its new ones included) in mode m:
+  // each of at least PF_KEYS_MIN of the keys that are there
+  __device__ __forceinline__ int chunks(int m, int len) const;
 };
 
 // Prefill: one block of two waves per (sequence, kv head, head quartet,
@@ -1189,9 +1192,12 @@ struct PrefillArgs {
 // Few query tiles behind a long context leave most of the chip idle while
 // each block walks its keys; the key range of a block is then cut into chunks
 // that leave (m, l, O) partials in a.part, merged by
-// attn_prefill_combine_kernel (pf_chunks decides).
+// attn_prefill_combine_kernel.  The grid has room for the chunks of a full
+// cache (pf_chunks); how many a sequence takes follows its length, which only
+// the device knows (PrefillArgs::chunks), and the blocks of the others return.
 constexpr int PF_WAVES = 2;
 constexpr int PF_MAX_CHUNKS = 8;
+constexpr int PF_KEYS_MIN = 256;               // keys a chunk
 constexpr int PF_HEADS = 2;                    // heads per wave
 constexpr int PF_RING = 40 * 1024 - 512;       // four blocks (eight waves) per CU
 // Lazy rescale threshold (log2 units): P' = fp16(p * s_v) with p <= 2^PF_TAU
@@ -1629,6 +1635,11 @@ __device__ __forceinline__ void stream_tiles_block(const CacheView &cv, int s, i
   pool(std::integral_constant<int, 3>{});
 }
 
+__device__ __forceinline__ int PrefillArgs::chunks(int m, int len) const {
+  const int keys = m == TRIROUTE_FULL ? len : min(len, w);
+  return max(1, min(m == TRIROUTE_FULL ? nsf : nsl, keys / PF_KEYS_MIN));
+}
+
 template <int DH, int G>
 __global__ __launch_bounds__(64 * PF_WAVES) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_prefill_mfma_kernel(PrefillArgs a) {
   using SG = StreamGeo<DH, G>;
@@ -1642,7 +1653,7 @@ __global__ __launch_bounds__(64 * PF_WAVES) __attribute__((amdgpu_waves_per_eu(2
   // blocks start in decreasing order of their key range
   const int pairs = a.B * a.Hkv * a.NQ, fulls = pairs * a.nsf * a.QT;
   const int m = int(blockIdx.x) < fulls ? TRIROUTE_FULL : TRIROUTE_LOCAL;
-  const int ns = m == TRIROUTE_FULL ? a.nsf : a.nsl, per_qt = pairs * ns;
+  const int per_qt = pairs * (m == TRIROUTE_FULL ? a.nsf : a.nsl);
   int r = m == TRIROUTE_FULL ? int(blockIdx.x) : int(blockIdx.x) - fulls;
   const int qt = a.QT - 1 - r / per_qt;
   r %= per_qt;
@@ -1653,7 +1664,9 @@ __global__ __launch_bounds__(64 * PF_WAVES) __attribute__((amdgpu_waves_per_eu(2
   const int g = r % a.Hkv, b = r / a.Hkv;
   const int s = a.seq_ids ? a.seq_ids[b] : b;
   if (s < 0 || s >= cv.n_seq) return;
-  const int base = cv.seq_len[s] - a.T;
+  const int slen = cv.seq_len[s], ns = a.chunks(m, slen);
+  if (chunk >= ns) return;
+  const int base = slen - a.T;
   // union of the quartet's key ranges (block-uniform: every wave computes it)
   int lo_u = INT_MAX, hi_u = -1;
   bool any = false;  // the block has a query
@@ -1782,12 +1795,13 @@ __global__ __launch_bounds__(256) void attn_prefill_combine_kernel(PrefillArgs a
   const int64_t rows = int64_t(a.B) * a.T * a.H, row = int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (row >= rows) return;
-  const int md = mode[row];
-  const int ns = md == TRIROUTE_FULL ? a.nsf : md == TRIROUTE_LOCAL ? a.nsl : 1;
-  if (ns <= 1) return;  // the attention block wrote the row itself (or it is zero)
   const int b = int(row / (int64_t(a.T) * a.H));
   const int s = a.seq_ids ? a.seq_ids[b] : b;
   if (s < 0 || s >= a.cv.n_seq) return;
+  const int md = mode[row];
+  if (md != TRIROUTE_FULL && md != TRIROUTE_LOCAL) return;
+  const int ns = a.chunks(md, a.cv.seq_len[s]);
+  if (ns <= 1) return;  // the attention block wrote the row itself
   const float2 *ml = (const float2 *)a.part + row * a.NS;
   const float *po = a.part + rows * a.NS * 2 + row * a.NS * DH;
   float v[PF_MAX_CHUNKS][DH / 64], m[PF_MAX_CHUNKS], l[PF_MAX_CHUNKS];
@@ -1877,14 +1891,18 @@ hipError_t launch_attn_mfma_decode(const triroute_cfg &cfg, const CacheView &cv,
   return hipGetLastError();
 }
 
-// Chunks of a block's key range, for `blocks` blocks of that mode over at
-// most `keys` keys: enough for PF_FILL two-wave blocks (four a CU) when a
-// routed mix gives the mode a third of the query tiles, each chunk of at
-// least PF_KEYS_MIN keys.  Measured on whole layers: 1.3B, 2 x 1000 tokens
+// The most chunks of a block's key range, for `blocks` blocks of that mode
+// over at most `keys` keys (a full cache, or the window): enough for PF_FILL
+// two-wave blocks (four a CU) when a routed mix gives the mode a third of the
+// query tiles, each chunk of at least PF_KEYS_MIN keys.  Measured on whole layers: 1.3B, 2 x 1000 tokens
 // behind 7001: 1240 us unsplit, 849-855 us with PF_FILL 512, 816-821 us with
 // 1024 and 2048; 410M, 64 tokens behind 8000: 453 -> 166 us; 160M, 8 x 256
 // tokens: 203 us unsplit and with 256 keys a chunk, 211 us with 128.
-constexpr int PF_FILL = 1024, PF_KEYS_MIN = 256;
+// Following the sequence's length instead of the room in its cache (of 32768):
+// 410M, 333 tokens 131 -> 127 us (a cache that is full 125), 160M, 8 x 256 170 ->
+// 166 (160), 1.3B, 4 x 512 575 -> 563 (563); the merge's launch is the rest.
+// (1.3B, 100 tokens, 28 blocks a mode: 296 in 8 chunks of 12 keys, 304 in one.)
+constexpr int PF_FILL = 1024;
 static int pf_chunks(int blocks, int keys, int most) {
   const int want = (3 * PF_FILL + blocks - 1) / blocks;
   return max(1, min(min(want, keys / PF_KEYS_MIN), most));

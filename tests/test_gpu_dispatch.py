@@ -79,7 +79,8 @@ def _small_layer(monkeypatch, **shape):
     (1, 1, 4, 1, 64, 100, 3000, None),       # one query tile, full mode split, local not
     (2, 17, 4, 2, 128, 600, 2500, None),     # both modes split, a ragged second query tile
     (1, 64, 6, 3, 64, 1000, 700, 2),         # paged; windows longer than some ranges
-    (3, 33, 8, 1, 64, 300, 0, None),         # two quartets, chunks without a key
+    (3, 33, 8, 1, 64, 300, 0, None),         # two quartets
+    (1, 700, 8, 1, 64, 300, 0, None),        # chunks without a key (early queries of a prompt)
     (1, 400, 4, 4, 128, 256, 1100, None),    # one head per kv head
 ])
 def test_prefill_split_key_ranges(monkeypatch, B, T, H, Hkv, dh, w, ctx, pages):
@@ -89,7 +90,7 @@ def test_prefill_split_key_ranges(monkeypatch, B, T, H, Hkv, dh, w, ctx, pages):
     L = _small_layer(monkeypatch, B=B, T=T, H=H, Hkv=Hkv, dh=dh, w=w)
     D = DeviceLayer(L)
     c, N = D.cfg, B * T
-    n_seq, cap = B + 2, 20000 if ctx else 4096   # chunk counts follow the capacity
+    n_seq, cap = B + 2, 20000 if ctx else 4096
     pg = None if pages is None else (pages, [64] * 4)
     cache = tr.KVCache(c, n_seq, cap, pages=pg)
     rng = gen.stream(41, "split", T, ctx)
@@ -179,6 +180,42 @@ def test_prefill_of_a_dropped_row(monkeypatch, act, T, len0, layer):
     assert_close(got["o"][0, neg:], ref.reshape(len(pos), -1), act, "o of the dropped row")
     np.testing.assert_array_equal(got["o"][1], whole["o"][1])
     assert np.isfinite(got["x_out"]).all()
+
+
+@pytest.mark.parametrize("B,T,H,Hkv,dh,w,lens", [
+    (1, 333, 16, 4, 64, 256, [0]),               # prefill: one chunk, two, and several
+    (2, 300, 4, 2, 128, 600, [0, 400]), (1, 64, 4, 1, 64, 900, [4000]),
+])
+def test_chunks_follow_the_content(monkeypatch, B, T, H, Hkv, dh, w, lens):
+    """The chunks of a key range follow the keys that are cached, not the room
+    in the cache: the same bits from a cache that is full after the call and
+    from one of 32768 positions."""
+    L = _small_layer(monkeypatch, B=B, T=T, H=H, Hkv=Hkv, dh=dh, w=w)
+    D = DeviceLayer(L)
+    c, N = D.cfg, B * T
+    res = []
+    for cap in (max(lens) + T, 32768):
+        cache = tr.KVCache(c, B, cap)
+        rng = gen.stream(44, "room", T, lens[0])
+        for b, n in enumerate(lens):
+            if n:
+                k, v = gen.kv_block(44 + b, n, Hkv, dh, "bf16", 0.8)
+                _append(c, cache, b, k, v, rng.integers(0, 4, n).astype(np.uint8), "bf16")
+        o = torch.full((N, H * dh), float("nan"), dtype=D.act, device=DEV)
+        x_out = torch.empty(N, 256, dtype=D.act, device=DEV)
+        taps = tr.Taps(o=o.data_ptr())
+        op = tr.OP_LAYER_DECODE if T == 1 else tr.OP_LAYER_PREFILL
+        ws = tr.workspace(c, op, B, T)
+        ws.fill_(0xFF)
+        print(f"content B={B} T={T} lens={lens} cap={cap}", flush=True)
+        if T == 1:
+            tr.layer_decode(c, B, D.x, D.psi, D.rw, D.dw, D.mw, cache, x_out, ws, taps=taps)
+        else:
+            tr.layer_prefill(c, B, T, D.x, D.psi, D.rw, D.dw, D.mw, cache, x_out, ws, taps=taps)
+        assert cache.status() == 0
+        res.append((npy(o), npy(x_out)))
+    for a, b in zip(*res):
+        np.testing.assert_array_equal(a, b)
 
 
 # ------------------------------------------------------- GEMM tile choices
