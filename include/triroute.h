@@ -335,7 +335,9 @@ int triroute_attn_prefill(const triroute_cfg *cfg, int B, int T, const int32_t *
 
 /* Sec. 3.2 (A) for the Sec. 3.8 left-to-right decode: as triroute_attn_prefill
  * for one new query per sequence (T = 1),
- * split over KV chunks with a log-sum-exp combine.
+ * split over KV chunks with a log-sum-exp combine (in bf16 the number of
+ * chunks follows B * Hkv and the cache's capacity, and with it the order of
+ * the fp32 sums behind o).
  *   q act [B, H*dh]; mode u8 [B, H]; o act [B, H*dh]. */
 int triroute_attn_decode(const triroute_cfg *cfg, int B, const int32_t *seq_ids, const void *q,
                          const triroute_kv_cache *cache, const uint8_t *mode, void *o, void *ws,

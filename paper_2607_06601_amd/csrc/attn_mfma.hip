@@ -1028,7 +1028,7 @@ __global__ __launch_bounds__(512, 1) void attn_decode_kernel(DecodeArgs a) {
       const int lb = bounds[bi][0], len = bounds[bi][1];
       const int lo = U == TRIROUTE_FULL ? 0 : lb;
       const int t0 = lo / TS, nt = (len + TS - 1) / TS - t0;
-      // nt * NS stays far below 2^31 (capacity / TS tiles, at most 16 chunks)
+      // nt * NS stays below 2^31 (at most 32 chunks, of fewer than 2^26 tiles)
       c0[bi] = t0 + nt * split / a.NS;
       nc[bi] = t0 + nt * (split + 1) / a.NS - c0[bi];
       wsum += nc[bi] * DEC_COST[bi];
@@ -1140,7 +1140,8 @@ __global__ __launch_bounds__(256) void attn_decode_combine_kernel(const float *_
   const float mj = in ? pp[lane * (DH + 2)] : -INFINITY;
   const float lj = in ? pp[lane * (DH + 2) + 1] : 0.f;
   const float M = wave_max(mj);
-  // a chunk without keys has m = -inf: weight 0
+  // (a chunk without keys has m = M0 and l = 0, and no weight beside one with
+  // keys; -inf: no chunk)
   const float wj = mj == -INFINITY ? 0.f : exp2f(mj - M);
   const float L = wave_sum(lj * wj);
   float acc[DH / 64];
@@ -1836,11 +1837,17 @@ __global__ __launch_bounds__(256) void attn_prefill_combine_kernel(PrefillArgs a
 // 256 / BH chunks, rounded down: a block more than the CUs starts a second
 // round (12 pairs of 50001 tokens, with the combine: 16 chunks 31.8 us, 20
 // 29.4 us, 24 38.4 us; 88 pairs of 16000: 2 chunks 60.0 us, 3 68.4 us; 200
-// pairs of 8000: one 35.6 us, 2 45.2 us).  A chunk keeps at least 6 tiles
-// (the cache's capacity bounds them): below that its start-up costs more
-// than the split saves (3 pairs of 3000 tokens, 47 tiles: 2 chunks 15.4 us,
-// 4 12.4 us, 8 11.5 us, 16 11.6 us), and two chunks do not pay for the
-// combine's launch (3 pairs of 501 tokens: 16 chunks 24 us, one 11 us).
+// pairs of 8000: one 35.6 us, 2 45.2 us).  A chunk of a full cache keeps at
+// least 6 tiles: finer ones gain nothing there (3 pairs of 3000 tokens, 47
+// tiles: 2 chunks 15.4 us, 4 12.4 us, 8 11.5 us, 16 11.6 us), and two do not
+// pay for the combine's launch, which the host saves for a cache that can
+// only take one.  A shorter context in a cache with room is cut finer, down
+// to chunks without a key.  That is the better half of it: the blocks are
+// there and the combine is launched, and counting chunks by the length on
+// the device (one below 18 tiles) was the slower (layers in a cache of 32768:
+// 410M, 8 x 700 tokens 87.8 -> 90.5 us, a cache that fits 86.6; 160M, 1 x 3000
+// 68.9 -> 70.6, fits 68.6; 1.3B, 4 x 300 169.1 -> 171.2, fits 167.7; 160M, 1 x
+// 501 69.5 -> 70.2, fits 66.3; attention alone, 3 x 50001: 27.7 -> 28.7).
 int decode_splits(int B, int Hkv, int capacity, int TS) {
   const int tiles = (capacity + TS - 1) / TS;
   const int ns = max(1, min(256 / (B * Hkv), DEC_MAX_SPLITS));

@@ -1180,8 +1180,11 @@ hipError_t mfma_qkv(const triroute_cfg &cfg, int B, int Tq, const void *n1,
   // Few tokens (decode): the product streams the weights; 32-row tiles one
   // head wide put one block on every head and row tile.  (Two K groups a
   // block would take 1.5 us off 9.3 on the 410M layer, but keys and values go
-  // into the cache, and every other tile here sums them in one order of K: a
-  // token's stored codes do not depend on how many tokens came with it.)
+  // into the cache, and every other tile here sums them in one order of K: for
+  // the same x a token's stored codes do not depend on how many tokens came
+  // with it.  Behind a layer they may: the O-projection and the experts pick
+  // tiles by the token count, and K groups or halves change the last bits of
+  // the x_out that the next layer stores keys and values of.)
   if (few_tiles(p.N, c128)) {
     if (p.dh == 64)
       return launch<QkvM, 32, 64, 2, 1, 64, 4>(p, cfg.d_model, (p.N + 31) / 32, (p.Ncols + 63) / 64, st);
@@ -1279,7 +1282,7 @@ hipError_t mfma_moe(const triroute_cfg &cfg, int N, const void *n2, const trirou
   if (r <= 24 && d >= 2048 && d % 128 == 0)
     // a long K: two K groups of three stages have more of the weights in
     // flight (1.3B, 32 to 100 tokens: the block 204 to 213 -> 193 to 202 us;
-    // 410M, K 1024: 40 -> 43)
+    // 410M, K 1024: 40 -> 43; nothing between the two was measured)
     err = launch<Moe1M, 32, 64, 2, 1, 64, 3, 2>(p1, d, Nk / 32 + E, (dff + 31) / 32, st);
   else if (r <= 24)
     err = launch<Moe1M, 32, 64, 2, 1, 64, 4>(p1, d, Nk / 32 + E, (dff + 31) / 32, st);

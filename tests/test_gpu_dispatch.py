@@ -1,5 +1,8 @@
-"""Edges of the size rules that choose between kernels and launch shapes, each
-against the CPU oracle (through the C ABI) at the repository's tolerances."""
+"""Edges of the size rules that choose between kernels and launch shapes, through
+the C ABI at the repository's tolerances: the attention and the cache's codes
+against the CPU oracle, the products and the controller against plain torch in
+fp32 or fp64 on the same operands, the lists and the chunk counts against the
+same work done by another route on the device."""
 import numpy as np
 import pytest
 import torch
@@ -86,7 +89,8 @@ def _small_layer(monkeypatch, **shape):
 def test_prefill_split_key_ranges(monkeypatch, B, T, H, Hkv, dh, w, ctx, pages):
     """The layer's attention (key ranges split over its scratch) against the
     stage call (never split) on the same queries, modes and cache: both round
-    the same sums, taken in another order, to bf16."""
+    the same sums, taken in another order, to bf16.  Then against the oracle's
+    attention over the same cached keys and values."""
     L = _small_layer(monkeypatch, B=B, T=T, H=H, Hkv=Hkv, dh=dh, w=w)
     D = DeviceLayer(L)
     c, N = D.cfg, B * T
@@ -94,18 +98,22 @@ def test_prefill_split_key_ranges(monkeypatch, B, T, H, Hkv, dh, w, ctx, pages):
     pg = None if pages is None else (pages, [64] * 4)
     cache = tr.KVCache(c, n_seq, cap, pages=pg)
     rng = gen.stream(41, "split", T, ctx)
-    ids = list(rng.permutation(n_seq)[:B])
+    ids, held = list(rng.permutation(n_seq)[:B]), {}
     if ctx:
         for s in ids:
             n = int(ctx * (0.5 + 0.5 * rng.random()))
             k, v = gen.kv_block(41 + int(s), n, Hkv, dh, "bf16", 0.8)
-            _append(c, cache, int(s), k, v, rng.integers(0, 4, n).astype(np.uint8), "bf16")
+            held[s] = (k, v, rng.integers(0, 4, n).astype(np.uint8))
+            _append(c, cache, int(s), *held[s], "bf16")
     if B > 2:
         ids[1] = n_seq                           # a row outside the cache: zeros
     sid = torch.tensor([int(s) for s in ids], dtype=torch.int32, device=DEV)
     t = dict(q=torch.empty(N, H * dh, dtype=D.act, device=DEV),
              o=torch.full((N, H * dh), float("nan"), dtype=D.act, device=DEV),
-             mode=torch.empty(N, H, dtype=torch.uint8, device=DEV))
+             mode=torch.empty(N, H, dtype=torch.uint8, device=DEV),
+             k=torch.empty(N, Hkv * dh, dtype=D.act, device=DEV),
+             v=torch.empty(N, Hkv * dh, dtype=D.act, device=DEV),
+             bit=torch.empty(N, dtype=torch.uint8, device=DEV))
     x_out = torch.empty(N, L["cfg"]["d"], dtype=D.act, device=DEV)
     ws = tr.workspace(c, tr.OP_LAYER_PREFILL, B, T)
     ws.fill_(0xFF)                               # scratch holds NaNs
@@ -127,6 +135,18 @@ def test_prefill_split_key_ranges(monkeypatch, B, T, H, Hkv, dh, w, ctx, pages):
     assert_close(npy(t["o"]), npy(o), "bf16", "o (split against unsplit)")
     if B > 2:
         assert not npy(t["o"]).reshape(B, -1)[1].any()
+    r = {n: npy(v).reshape(B, T, *v.shape[1:]) for n, v in t.items()}
+    for b, s in enumerate(ids):
+        if s == n_seq:
+            continue
+        k, v = (r[n][b].reshape(T, Hkv, dh) for n in "kv")
+        bits = r["bit"][b]
+        if s in held:
+            k, v, bits = (np.concatenate(p) for p in zip(held[s], (k, v, bits)))
+        khat, vhat, _ = oracle.layer.store_kv(k, v, bits, dict(G=64))
+        ref = oracle.attention_seq(r["q"][b].reshape(T, H, dh).astype(np.float64),
+                                   np.arange(len(bits) - T, len(bits)), khat, vhat, r["mode"][b], w)
+        assert_close(r["o"][b], ref.reshape(T, -1), "bf16", f"o[{b}] (against the oracle)")
 
 
 @pytest.mark.parametrize("act,T,len0,layer", [
@@ -183,7 +203,7 @@ def test_prefill_of_a_dropped_row(monkeypatch, act, T, len0, layer):
 
 
 @pytest.mark.parametrize("B,T,H,Hkv,dh,w,lens", [
-    (1, 333, 16, 4, 64, 256, [0]),               # prefill: one chunk, two, and several
+    (1, 333, 16, 4, 64, 256, [0]),               # one chunk, two, and several
     (2, 300, 4, 2, 128, 600, [0, 400]), (1, 64, 4, 1, 64, 900, [4000]),
 ])
 def test_chunks_follow_the_content(monkeypatch, B, T, H, Hkv, dh, w, lens):
@@ -204,18 +224,47 @@ def test_chunks_follow_the_content(monkeypatch, B, T, H, Hkv, dh, w, lens):
         o = torch.full((N, H * dh), float("nan"), dtype=D.act, device=DEV)
         x_out = torch.empty(N, 256, dtype=D.act, device=DEV)
         taps = tr.Taps(o=o.data_ptr())
-        op = tr.OP_LAYER_DECODE if T == 1 else tr.OP_LAYER_PREFILL
-        ws = tr.workspace(c, op, B, T)
+        ws = tr.workspace(c, tr.OP_LAYER_PREFILL, B, T)
         ws.fill_(0xFF)
         print(f"content B={B} T={T} lens={lens} cap={cap}", flush=True)
-        if T == 1:
-            tr.layer_decode(c, B, D.x, D.psi, D.rw, D.dw, D.mw, cache, x_out, ws, taps=taps)
-        else:
-            tr.layer_prefill(c, B, T, D.x, D.psi, D.rw, D.dw, D.mw, cache, x_out, ws, taps=taps)
+        tr.layer_prefill(c, B, T, D.x, D.psi, D.rw, D.dw, D.mw, cache, x_out, ws, taps=taps)
         assert cache.status() == 0
         res.append((npy(o), npy(x_out)))
     for a, b in zip(*res):
         np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("H,Hkv,dh", [(4, 2, 64), (8, 1, 128)])  # heads packed, a head a column
+def test_decode_chunks_of_a_mixed_batch(H, Hkv, dh):
+    """Long, short and empty rows and one outside the cache in one launch of
+    many chunks, most of them without a key in the short rows, over scratch that
+    holds NaNs: each row against the oracle."""
+    lens, ids, act, w = [3000, 40, 0, 1500, 0], [0, 1, 2, 9, 3], "bf16", 200
+    c = tr.make_cfg(256, H, Hkv, dh, w, 4, 1, 512, 64, act)
+    B = len(ids)
+    rng = gen.stream(45, "mixed", H)
+    modes = rng.choice(3, size=(B, H), p=[0.1, 0.3, 0.6]).astype(np.uint8)
+    q = gen.to_act(gen.normal(45, "mixed_q", (B, H, dh), 0.8), act)
+    cache, kv = tr.KVCache(c, len(lens), 20000), {}
+    for s, n in enumerate(lens):
+        if n:
+            k, v = gen.kv_block(45 + s, n, Hkv, dh, act, 0.8)
+            kv[s] = (k, v, rng.integers(0, 4, n).astype(np.uint8))
+            _append(c, cache, s, *kv[s], act)
+    o = torch.full((B, H * dh), float("nan"), dtype=torch_act(act), device=DEV)
+    ws = tr.workspace(c, tr.OP_ATTN_DECODE, B, 1)
+    ws.fill_(0xFF)
+    tr.attn_decode(c, B, to_dev(q.reshape(B, -1), torch_act(act)), cache, to_dev(modes, torch.uint8),
+                   o, ws=ws, seq_ids=torch.tensor(ids, dtype=torch.int32, device=DEV))
+    og = npy(o).reshape(B, H, dh)
+    for r, s in enumerate(ids):
+        if s not in kv:
+            assert not og[r].any()
+            continue
+        khat, vhat, _ = oracle.layer.store_kv(*kv[s], dict(G=64))
+        ref = oracle.attention_seq(np.asarray(q[r:r + 1], np.float64), np.array([lens[s] - 1]), khat,
+                                   vhat, modes[r:r + 1], w)[0]
+        assert_close(og[r], ref, act, f"o[{r}]")
 
 
 # ------------------------------------------------------- GEMM tile choices
